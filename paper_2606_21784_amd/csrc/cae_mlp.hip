@@ -7,8 +7,8 @@
 //
 // Precision: weights, inputs, hidden activations and back-propagated gradients are stored in
 // bfloat16 (round to nearest even); every product is accumulated in fp32 on the matrix cores
-// (v_mfma_f32_16x16x16bf16_1k in the general GEMM and the fused inference kernel, gfx950's
-// v_mfma_f32_16x16x32_bf16 in the fused training step); biases, pre-activations, outputs, weight
+// (gfx950's v_mfma_f32_32x32x16_bf16 and v_mfma_f32_16x16x32_bf16; the fused inference kernel
+// v_mfma_f32_16x16x16bf16_1k, whose chains give the same bits); biases, pre-activations, outputs, weight
 // gradients and the Adam state are fp32.  Parameter layout (row-major, input index first):
 //   W1[d_in][H], b1[H], W2[H][H], b2[H], W3[H][d_out], b3[d_out]
 // and the bfloat16 weight copies are W1, W2, W3 in the same layouts, back to back, followed by
@@ -21,6 +21,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <mutex>
+#include <type_traits>
 
 #include "cae.h"
 
@@ -37,6 +38,9 @@ __device__ __forceinline__ uint16_t f2bf(float f)  // round to nearest even
     return (uint16_t)(u >> 16);
 }
 
+// The same rounding in one instruction, for values computed here (a NaN stays a NaN).
+__device__ __forceinline__ uint16_t f2bf_hw(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
 
 __device__ __forceinline__ float dsilu(float z)
@@ -45,125 +49,628 @@ __device__ __forceinline__ float dsilu(float z)
     return s * (1.0f + z * (1.0f - s));
 }
 
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// Eight bfloat16 (or four floats) at any address of their element's alignment: the caller's
+// buffers carry no stronger promise, and gfx950 loads them in one instruction either way.
+typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(2), may_alias));
+typedef uint32_t v2u_any __attribute__((ext_vector_type(2), aligned(2), may_alias));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4), may_alias));
+
+__device__ __forceinline__ uint4 ld8u(const uint16_t *p)
+{
+    const v4u_any v = *reinterpret_cast<const v4u_any *>(p);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// The same at a uniform base and a 32-bit byte offset per lane (no address arithmetic per load).
+__device__ __forceinline__ uint4 ld8u(const uint16_t *base, uint32_t bytes)
+{
+    return ld8u(reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + bytes));
+}
+
+__device__ __forceinline__ v8bf ld8(const uint16_t *p)  // eight bfloat16, 16-byte aligned
+{
+    return __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(p));
+}
+
+// Four bfloat16 of a k-major LDS tile, transposed: within each 16 lanes, lane i addresses row
+// i / 4, columns 4 (i % 4) .. + 3 of a 4 x 16 block and receives column i of its four rows.
+typedef short v4h __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4h lds_v4h;
+
+__device__ __forceinline__ v8bf ld8_tr(const uint16_t *p, uint32_t ld)  // rows r .. r+3 and r+4 .. r+7
+{
+    const v4h lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4h *)p);
+    const v4h hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4h *)(p + 4u * ld));
+    return __builtin_bit_cast(v8bf, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// One matrix-core instruction on an MF x MF tile: 32x32x16 or 16x16x32.  Both add their products
+// in increasing k, four at a time, so a chain over k gives the same bits with either (and with
+// the half-depth forms); every product that a bfloat16 rounding follows is one such chain.
+template <int MF>
+struct Mfma;
+template <>
+struct Mfma<32> {
+    typedef v16f acc_t;
+    static constexpr uint32_t kDepth = 16, kRegs = 16;
+    static __device__ __forceinline__ acc_t mac(v8bf a, v8bf b, acc_t c)
+    {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ uint32_t row(uint32_t i, uint32_t lane)
+    {
+        return 8u * (i >> 2) + 4u * (lane >> 5) + (i & 3u);
+    }
+};
+template <>
+struct Mfma<16> {
+    typedef v4f acc_t;
+    static constexpr uint32_t kDepth = 32, kRegs = 4;
+    static __device__ __forceinline__ acc_t mac(v8bf a, v8bf b, acc_t c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ uint32_t row(uint32_t i, uint32_t lane) { return 4u * (lane >> 4) + i; }
+};
+
+// LDS tiles.  A row-major operand keeps kBK consecutive k per row, padded by 8 elements (rows of
+// 144 bytes: the 16-byte fragment reads of a wave spread over the banks).  A k-major operand keeps
+// its rows of consecutive columns, padded by 32 elements, so the four rows of a transposing read
+// start a quarter of the banks apart.
+constexpr uint32_t kBK = 64;
+constexpr uint32_t kLdR = kBK + 8u;
+constexpr uint32_t kPadK = 32;
+// Operand blocks in registers or on their way there (a third measured 5 % slower).
+constexpr uint32_t kAhead = 2;
+
+// Fragment of MF rows (or columns) starting at `at`, reduction elements from kk.
+template <int MF, bool KMAJOR>
+__device__ __forceinline__ v8bf frag(const uint16_t *tile, uint32_t ld, uint32_t at, uint32_t kk, uint32_t lane)
+{
+    if constexpr (!KMAJOR) {
+        return ld8(tile + (at + (lane & (MF - 1u))) * ld + kk + 8u * (lane / MF));
+    } else {
+        const uint32_t i = lane & 15u, q = lane >> 4;
+        const uint32_t kg = MF == 32 ? q >> 1 : q, cg = MF == 32 ? q & 1u : 0u;
+        return ld8_tr(tile + (kk + 8u * kg + (i >> 2)) * ld + at + 16u * cg + 4u * (i & 3u), ld);
+    }
+}
+
+__device__ __forceinline__ uint4 keep(bool in, const uint4 &v)  // v, or zero
+{
+    return make_uint4(in ? v.x : 0u, in ? v.y : 0u, in ? v.z : 0u, in ? v.w : 0u);
+}
+
+// Contiguous ranges of tiles per XCD (workgroups are dealt round-robin over the 8 XCDs, each with
+// its own L2): tile index of workgroup `b` of `n`.
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n)
+{
+    const uint32_t x = b & 7u, per = n >> 3, rem = n & 7u;
+    return x * per + min(x, rem) + (b >> 3);
+}
+
 enum Epi : int {
-    EPI_HIDDEN = 0,  // z = acc + bias -> Z (f32), H = bf16(silu(z))
-    EPI_OUTPUT = 1,  // y = acc + bias -> f32
-    EPI_DSILU = 2,   // dz = bf16(acc * silu'(Z))
-    EPI_F32 = 3,     // acc -> f32
+    EPI_HIDDEN = 0,  // z = acc + bias -> Z (f32), O = bf16(silu(z))
+    EPI_DSILU = 1,   // O = bf16(acc * silu'(Z))
 };
 
-struct GemmArgs {
-    const uint16_t *A;  // bf16, M x K (or K x M when transposed)
-    const uint16_t *B;  // bf16, K x N (or N x K when transposed)
-    uint32_t lda, ldb;
+struct LayerArgs {
+    const uint16_t *A;   // bfloat16 rows (M x K, contiguous) ...
+    const float *Af;     // ... or fp32 rows converted on the way in (K <= 64), and ...
+    uint16_t *Acopy;     // ... the bfloat16 copy of them kept for the backward pass, in rows of
+    uint32_t ldc;        //     ldc elements (K rounded up to 16), zero past K
+    const uint16_t *B;   // row n of K consecutive elements, or (k-major) row k of N
     uint32_t M, N, K;
-    uint32_t ones_row;  // A has one extra row M of ones (its output row is the column sum of B)
-    uint32_t kchunk;    // K range per blockIdx.y (split K); partial sums go to Of + y * (M+1) * ldo
-    const float *bias;  // EPI_HIDDEN / EPI_OUTPUT
-    const float *Zin;   // EPI_DSILU: pre-activations (M x N, ld = ldo)
-    float *Of;          // f32 output (Z, y, or gradient), ld = ldo
-    uint16_t *Ob;       // bf16 output (H or dz), ld = ldo
-    uint32_t ldo;
+    const float *bias;   // EPI_HIDDEN
+    float *Z;            // EPI_HIDDEN: written; EPI_DSILU: read (M x N)
+    uint16_t *O;         // M x N
 };
 
-// C = A * B with one wave per 16x16 output tile (four tiles per workgroup).  MFMA operand
-// layout (16x16x16): lane l holds A[l%16][4*(l/16)+t] and B[4*(l/16)+t][l%16], t = 0..3, and
-// receives C[4*(l/16)+t][l%16].
-template <bool TA, bool TB, int EPI>
-__global__ void __launch_bounds__(256) mlp_gemm(const GemmArgs g)
+// One layer product of the hidden width, C = A B with a fused epilogue: four waves per workgroup
+// in a 2 x 2 arrangement of WM x WN output tiles each, operands staged through LDS in blocks of 64
+// of the reduction, the next block's global loads in flight during the current block's products.
+//   AF32: A is fp32 and short (the input, or the output gradient): one block.
+//   KMAJOR: B is read k-major through transposing LDS reads (W1, W2 forward); otherwise its rows
+//   are the reduction (W2 backward), or short rows of any length (W3 backward, AF32).
+// Every output is one chain over the reduction in increasing k, whatever the tile.  At 4096 x 1024
+// x 1024 the forward product takes 21.5 us and the backward one 20.3 (one wave per 16 x 16 tile
+// with two-byte operand loads: 475 and 882 us), of which the products are about half (matrix cores
+// busy 8.4e6 of 1.9e7 SIMD cycles); the other half is the exponentials and the stores of the
+// epilogue, which the short products (12 and 9 us, from 35 and 20) consist of.
+template <int WM, int WN, bool AF32, bool KMAJOR, int EPI>
+__global__ void __launch_bounds__(256) mlp_layer(const LayerArgs g)
 {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = threadIdx.x >> 6;
-    const uint32_t Mr = g.M + g.ones_row;  // rows of the output
-    const uint32_t tiles_n = (g.N + 15u) / 16u;
-    const uint32_t tile = blockIdx.x * 4u + wave;
-    const uint32_t ti = tile / tiles_n, tj = tile % tiles_n;
-    if (ti * 16u >= Mr) return;
-    const uint32_t r = lane & 15u, grp = lane >> 4;
-    const uint32_t row = ti * 16u + r;  // A row this lane feeds
-    const uint32_t col = tj * 16u + r;  // B column this lane feeds
-    const uint32_t kbeg = blockIdx.y * g.kchunk;
-    const uint32_t kend = min(g.K, kbeg + g.kchunk);
-    v4f acc = {0.f, 0.f, 0.f, 0.f};
-    for (uint32_t k0 = kbeg; k0 < kend; k0 += 16u) {
-        v4s a, b;
+    constexpr int MF = WM >= 32 ? 32 : 16;
+    constexpr uint32_t MI = WM / MF, NI = WN / MF, BM = 2 * WM, BN = 2 * WN;
+    using MM = Mfma<MF>;
+    constexpr uint32_t kBufs = AF32 ? 1u : 2u;
+    constexpr uint32_t kLdB = KMAJOR ? BN + kPadK : kLdR;
+    constexpr uint32_t kTileB = KMAJOR ? kBK * kLdB : BN * kLdR;
+    __shared__ __align__(16) uint16_t sA[kBufs * BM * kLdR];
+    __shared__ __align__(16) uint16_t sB[kBufs * kTileB];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t wm = wave >> 1, wn = wave & 1u;
+    const uint32_t tn = (g.N + BN - 1u) / BN;
+    const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    const uint32_t row0 = tile / tn * BM, col0 = tile % tn * BN;
+
+    // 16-byte chunks of each operand block per thread, at 32-bit offsets from the block's uniform
+    // base.  Every load is issued without a condition: rows and columns past the end are clamped
+    // and reach only outputs that are not stored, a reduction block past the end is the last one
+    // again, and what its chunks read past the reduction (the next row; the hidden arrays have
+    // kPadRows of slack, W2 is followed by W3 and W2T) is zeroed on its way into LDS.  A masked
+    // load would make the compiler drain the loads still in flight.
+    constexpr uint32_t CA = BM / 32u, CB = BN / 32u, NB = BN / 8u;
+    constexpr uint32_t PD = AF32 ? 1u : kAhead;
+    const uint32_t nk = AF32 ? 1u : (g.K + kBK - 1u) / kBK, klast = (nk - 1u) * kBK;
+    uint4 sa[PD][CA], sb[PD][CB];
+    uint32_t oa[CA], ob[CB], obt[CB];
+    const uint32_t ka = 8u * (tid & 7u);  // a row-major chunk's first reduction element in its block
+    const uint16_t *Ab = nullptr, *Bb = KMAJOR ? g.B + col0 : g.B + (size_t)col0 * g.K;
+    if constexpr (!AF32) {
+        Ab = g.A + (size_t)row0 * g.K;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const uint32_t k = k0 + 4u * grp + (uint32_t)t;
-            uint16_t av = 0, bv = 0;
-            if (k < kend) {
-                if (row < g.M) av = TA ? g.A[(size_t)k * g.lda + row] : g.A[(size_t)row * g.lda + k];
-                else if (row == g.M && g.ones_row) av = 0x3F80u;  // bfloat16 1.0
-                if (col < g.N) bv = TB ? g.B[(size_t)col * g.ldb + k] : g.B[(size_t)k * g.ldb + col];
-            }
-            a[t] = (short)av;
-            b[t] = (short)bv;
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+        for (uint32_t c = 0; c < CA; ++c) oa[c] = 2u * (min((tid + 256u * c) >> 3, g.M - 1u - row0) * g.K + ka);
     }
-    const uint32_t j = tj * 16u + r;
-    if (j >= g.N) return;
-    float *Of = g.Of + (size_t)blockIdx.y * Mr * g.ldo;  // split-K partial (y = 0 when not split)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const uint32_t i = ti * 16u + 4u * grp + (uint32_t)t;
-        if (i >= Mr) continue;
-        const size_t o = (size_t)i * g.ldo + j;
-        if constexpr (EPI == EPI_HIDDEN) {
-            const float z = acc[t] + g.bias[j];
-            g.Of[o] = z;
-            g.Ob[o] = f2bf(silu(z));
-        } else if constexpr (EPI == EPI_OUTPUT) {
-            g.Of[o] = acc[t] + g.bias[j];
-        } else if constexpr (EPI == EPI_DSILU) {
-            g.Ob[o] = f2bf(acc[t] * dsilu(g.Zin[o]));
+    for (uint32_t c = 0; c < CB; ++c) {
+        const uint32_t e = tid + 256u * c;
+        if constexpr (KMAJOR) {  // ob: a whole block, obt: the last one, its rows clamped
+            const uint32_t n = min(8u * (e % NB), g.N - 8u - col0), kr = e / NB;
+            ob[c] = 2u * (kr * g.N + n);
+            obt[c] = 2u * (min(kr, g.K - 1u - klast) * g.N + n);
         } else {
-            Of[o] = acc[t];
+            ob[c] = obt[c] = 2u * (min(e >> 3, g.N - 1u - col0) * g.K + ka);
+        }
+    }
+    auto fetch = [&](uint32_t k0, uint4 (&ra)[CA], uint4 (&rb)[CB]) {
+        const uint32_t k = min(k0, klast);
+        if constexpr (!AF32) {
+#pragma unroll
+            for (uint32_t c = 0; c < CA; ++c) ra[c] = ld8u(Ab + k, oa[c]);
+        }
+        if constexpr (KMAJOR) {
+            const bool tail = k + kBK > g.K;
+#pragma unroll
+            for (uint32_t c = 0; c < CB; ++c) rb[c] = ld8u(Bb + (size_t)k * g.N, tail ? obt[c] : ob[c]);
+        } else if constexpr (!AF32) {
+#pragma unroll
+            for (uint32_t c = 0; c < CB; ++c) rb[c] = ld8u(Bb + k, ob[c]);
+        }
+    };
+    auto store = [&](uint32_t buf, uint32_t k0, const uint4 (&ra)[CA], const uint4 (&rb)[CB], auto whole) {
+        constexpr bool kWhole = decltype(whole)::value;
+        uint16_t *la = sA + buf * BM * kLdR, *lb = sB + buf * kTileB;
+        const bool in = kWhole || k0 + ka < g.K;
+        if constexpr (!AF32) {
+#pragma unroll
+            for (uint32_t c = 0; c < CA; ++c)
+                *reinterpret_cast<uint4 *>(la + ((tid + 256u * c) >> 3) * kLdR + ka) = keep(in, ra[c]);
+        }
+        if constexpr (KMAJOR) {
+#pragma unroll
+            for (uint32_t c = 0; c < CB; ++c) {
+                const uint32_t e = tid + 256u * c, kr = e / NB;
+                *reinterpret_cast<uint4 *>(lb + kr * kLdB + 8u * (e % NB)) = keep(kWhole || k0 + kr < g.K, rb[c]);
+            }
+        } else if constexpr (!AF32) {
+#pragma unroll
+            for (uint32_t c = 0; c < CB; ++c)
+                *reinterpret_cast<uint4 *>(lb + ((tid + 256u * c) >> 3) * kLdR + ka) = keep(in, rb[c]);
+        }
+    };
+    auto stage = [&](uint32_t buf, uint32_t k0, const uint4 (&ra)[CA], const uint4 (&rb)[CB]) {
+        if (k0 + kBK <= g.K) store(buf, k0, ra, rb, std::true_type{});
+        else store(buf, k0, ra, rb, std::false_type{});
+    };
+
+    const uint32_t kpad = (min(g.K, kBK) + MM::kDepth - 1u) / MM::kDepth * MM::kDepth;
+#pragma unroll
+    for (uint32_t u = 0; u < PD; ++u) fetch(u * kBK, sa[u], sb[u]);
+    if constexpr (AF32) {
+        // short rows: convert, keep the copy (one column of workgroups), zero the padding; eight
+        // loads in flight per thread
+        const uint32_t ks = kpad <= 16u ? 4u : (kpad <= 32u ? 5u : 6u), kp = 1u << ks;
+        for (uint32_t e0 = tid; e0 < BM << ks; e0 += 2048u) {
+            float v[8];
+#pragma unroll
+            for (uint32_t c = 0; c < 8u; ++c) {
+                const uint32_t e = e0 + 256u * c, r = e >> ks, k = e & (kp - 1u);
+                v[c] = (e < BM << ks && row0 + r < g.M && k < g.K) ? g.Af[(size_t)(row0 + r) * g.K + k] : 0.f;
+            }
+#pragma unroll
+            for (uint32_t c = 0; c < 8u; ++c) {
+                const uint32_t e = e0 + 256u * c, r = e >> ks, k = e & (kp - 1u);
+                if (e >= BM << ks) continue;
+                const uint16_t b = f2bf(v[c]);
+                sA[r * kLdR + k] = b;
+                if (col0 == 0u && row0 + r < g.M && k < g.ldc) g.Acopy[(size_t)(row0 + r) * g.ldc + k] = b;
+            }
+        }
+        if constexpr (!KMAJOR) {
+            for (uint32_t e = tid; e < BN << ks; e += 256u) {
+                const uint32_t r = e >> ks, k = e & (kp - 1u);
+                sB[r * kLdR + k] = (col0 + r < g.N && k < g.K) ? g.B[(size_t)(col0 + r) * g.K + k] : (uint16_t)0;
+            }
+        }
+    }
+    stage(0, 0u, sa[0], sb[0]);
+    __syncthreads();
+
+    typename MM::acc_t acc[MI][NI];
+#pragma unroll
+    for (uint32_t i = 0; i < MI; ++i)
+#pragma unroll
+        for (uint32_t j = 0; j < NI; ++j)
+#pragma unroll
+            for (uint32_t t = 0; t < MM::kRegs; ++t) acc[i][j][t] = 0.f;
+    auto step = [&](const uint16_t *pa, const uint16_t *pb, uint32_t kk) {
+        v8bf fa[MI], fb[NI];
+#pragma unroll
+        for (uint32_t i = 0; i < MI; ++i) fa[i] = frag<MF, false>(pa, kLdR, wm * WM + i * MF, kk, lane);
+#pragma unroll
+        for (uint32_t j = 0; j < NI; ++j) fb[j] = frag<MF, KMAJOR>(pb, kLdB, wn * WN + j * MF, kk, lane);
+#pragma unroll
+        for (uint32_t i = 0; i < MI; ++i)
+#pragma unroll
+            for (uint32_t j = 0; j < NI; ++j) acc[i][j] = MM::mac(fa[i], fb[j], acc[i][j]);
+    };
+    if constexpr (AF32) {
+        for (uint32_t kk = 0; kk < kpad; kk += MM::kDepth) step(sA, sB, kk);
+    } else {
+        // block t is computed from LDS while block t + 1 waits in registers and the loads of the
+        // PD - 1 blocks after it are in flight (blocks past the reduction are zero)
+        for (uint32_t t0 = 0; t0 < nk; t0 += PD) {
+#pragma unroll
+            for (uint32_t u = 0; u < PD; ++u) {
+                const uint32_t t = t0 + u, buf = PD % 2u ? t & 1u : u & 1u;
+                fetch((t + PD) * kBK, sa[u], sb[u]);
+                __builtin_amdgcn_sched_barrier(0);  // the loads leave before the products
+#pragma unroll
+                for (uint32_t kk = 0; kk < kBK; kk += MM::kDepth)
+                    step(sA + buf * BM * kLdR, sB + buf * kTileB, kk);
+                stage(buf ^ 1u, (t + 1u) * kBK, sa[(u + 1u) % PD], sb[(u + 1u) % PD]);
+                __syncthreads();
+            }
+        }
+    }
+
+    // epilogue: rows and columns checked only in the tiles at the edges (a branch per element makes
+    // the compiler wait for every store before the next element)
+    float bn[NI];
+#pragma unroll
+    for (uint32_t j = 0; j < NI; ++j) {
+        bn[j] = 0.f;
+        if constexpr (EPI == EPI_HIDDEN) bn[j] = g.bias[min(col0 + wn * WN + j * MF + (lane & (MF - 1u)), g.N - 1u)];
+    }
+    float *Zt = g.Z + (size_t)row0 * g.N + col0;
+    uint16_t *Ot = g.O + (size_t)row0 * g.N + col0;
+    auto finish = [&](auto whole) {
+        constexpr bool kWhole = decltype(whole)::value;
+        const uint32_t mr = g.M - row0, nr = g.N - col0;  // rows and columns from the tile's origin
+#pragma unroll
+        for (uint32_t j = 0; j < NI; ++j) {
+            const uint32_t n = wn * WN + j * MF + (lane & (MF - 1u));
+            if (!kWhole && n >= nr) continue;
+#pragma unroll
+            for (uint32_t i = 0; i < MI; ++i) {
+                const uint32_t m0 = wm * WM + i * MF;
+                float z[MM::kRegs];
+                if constexpr (EPI == EPI_DSILU) {  // every load before the first use
+#pragma unroll
+                    for (uint32_t t = 0; t < MM::kRegs; ++t) {
+                        const uint32_t m = m0 + MM::row(t, lane);
+                        z[t] = Zt[(kWhole ? m : min(m, mr - 1u)) * g.N + n];
+                    }
+                }
+#pragma unroll
+                for (uint32_t t = 0; t < MM::kRegs; ++t) {
+                    const uint32_t m = m0 + MM::row(t, lane);
+                    if (!kWhole && m >= mr) continue;
+                    const uint32_t o = m * g.N + n;
+                    if constexpr (EPI == EPI_HIDDEN) {
+                        const float zv = acc[i][j][t] + bn[j];
+                        Zt[o] = zv;
+                        Ot[o] = f2bf_hw(silu(zv));
+                    } else {
+                        Ot[o] = f2bf_hw(acc[i][j][t] * dsilu(z[t]));
+                    }
+                }
+            }
+        }
+    };
+    if (row0 + BM <= g.M && col0 + BN <= g.N) finish(std::true_type{});
+    else finish(std::false_type{});
+}
+
+// Output layer y = h W3 + b3: 16 rows per workgroup.  All four waves bring the rows and W3 (rows
+// of 16 columns, read transposed) into LDS, one wave runs the chain over H.
+__global__ void __launch_bounds__(256) mlp_out(const uint16_t *h, const uint16_t *W3, const float *b3, float *y,
+                                               uint32_t M, uint32_t H, uint32_t dout)
+{
+    extern __shared__ __align__(16) uint16_t olds[];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, r = lane & 15u, gq = lane >> 4;
+    const uint32_t Hp = (H + 31u) & ~31u, ldh = Hp + 8u;
+    uint16_t *hs = olds, *w3s = olds + 16u * ldh;  // [16][ldh], [Hp][16]
+    const uint32_t row0 = blockIdx.x * 16u, hc = Hp / 8u;
+    for (uint32_t e0 = tid; e0 < 16u * hc; e0 += 2048u) {
+        uint4 v[8];
+#pragma unroll
+        for (uint32_t c = 0; c < 8u; ++c) {
+            const uint32_t e = e0 + 256u * c, rr = e / hc, k = 8u * (e % hc);
+            v[c] = ld8u(h + (size_t)min(row0 + min(rr, 15u), M - 1u) * H + min(k, H - 8u));
+        }
+#pragma unroll
+        for (uint32_t c = 0; c < 8u; ++c) {
+            const uint32_t e = e0 + 256u * c;
+            if (e < 16u * hc) *reinterpret_cast<uint4 *>(hs + e / hc * ldh + 8u * (e % hc)) = keep(8u * (e % hc) < H, v[c]);
+        }
+    }
+    if (dout == 16u) {
+        for (uint32_t e = tid; e < Hp * 2u; e += 256u)
+            *reinterpret_cast<uint4 *>(w3s + 8u * e) = e < H * 2u ? ld8u(W3 + 8u * e) : make_uint4(0, 0, 0, 0);
+    } else {
+        for (uint32_t e = tid; e < Hp * 16u; e += 256u) {
+            const uint32_t k = e >> 4, c = e & 15u;
+            w3s[e] = (k < H && c < dout) ? W3[(size_t)k * dout + c] : (uint16_t)0;
+        }
+    }
+    __syncthreads();
+    if (tid >= 64u) return;
+    v4f acc = {0.f, 0.f, 0.f, 0.f};
+    for (uint32_t k0 = 0; k0 < Hp; k0 += 32u)
+        acc = Mfma<16>::mac(frag<16, false>(hs, ldh, 0u, k0, lane), frag<16, true>(w3s, 16u, 0u, k0, lane), acc);
+    if (r < dout) {
+#pragma unroll
+        for (uint32_t t = 0; t < 4u; ++t)
+            if (row0 + 4u * gq + t < M) y[(size_t)(row0 + 4u * gq + t) * dout + r] = acc[t] + b3[r];
+    }
+}
+
+// Weight gradients [A; 1]^T B over the batch (A: a layer's input, B: its output gradient, both
+// batch-major, so both operands are k-major LDS tiles read transposed; the row of ones gives the
+// bias gradient).  The batch is cut into chunks of at most 256 rows (more beyond 16384 rows): each
+// chunk is one matrix-core chain and the chunks' results are added in chunk order, so a gradient
+// does not depend on how the chunks are spread over workgroups.  One launch holds the tiles of
+// all three gradients.  A workgroup either takes one chunk and leaves its result for grad_reduce,
+// or (parts = 1) takes every chunk of its tile and adds them in registers.
+// At a batch of 4096 and H = 1024 the launch takes 45 us (two-byte strided loads, three products
+// and three sums in six launches: 155 us): one workgroup of four waves per CU, so the time is
+// that of 64 blocks' chains of LDS write, barrier, transposing reads and matrix-core steps.
+struct GradArgs {
+    const uint16_t *x, *h1, *h2, *dy, *dz2, *dz1;
+    uint32_t batch, din, H, dout;
+    uint32_t parts, chunk;
+    uint32_t tiles1, tiles2, tiles3;  // tiles of W1, W2, W3
+    float *o1, *o2, *o3;              // part 0 of each gradient, its bias row after its last row
+    size_t stride;                    // floats between parts
+};
+
+// One BM x BN tile by four waves (WR along M), wave tiles of 32 x 32 products.  lda, ldb: the
+// operands' row lengths, multiples of 16 (the rows are zero past M and N).
+template <uint32_t BM, uint32_t BN, uint32_t WR>
+__device__ __forceinline__ void grad_tile(uint16_t *lds, const uint16_t *A, const uint16_t *B, uint32_t lda,
+                                          uint32_t ldb, uint32_t M, uint32_t N, uint32_t m0, uint32_t n0,
+                                          uint32_t kbeg, uint32_t kend, uint32_t chunk, float *out)
+{
+    constexpr uint32_t WC = 4u / WR, MI = BM / WR / 32u, NI = BN / WC / 32u;
+    constexpr uint32_t kLdA = BM + kPadK, kLdB = BN + kPadK, kTA = kBK * kLdA, kTB = kBK * kLdB;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6)), wm = wave / WC, wn = wave % WC;
+    uint16_t *sA = lds, *sB = lds + 2u * kTA;
+    constexpr uint32_t CA = kBK * BM / 8u / 256u, CB = kBK * BN / 8u / 256u;
+    const bool bias = m0 == 0u && wm == 0u;  // this wave also forms the row of ones of its columns
+    // blocks of 64 batch rows, nb to a chunk; as in mlp_layer, loads are not masked (the arrays have
+    // kPadRows rows of slack), and rows past the chunk's end (ce) are zeroed on their way into LDS
+    const uint32_t nb = (chunk + kBK - 1u) / kBK;
+    struct Block {
+        uint32_t c0, j;  // the chunk's first row, the block in it
+    };
+    auto next = [&](Block b) { return b.j + 1u < nb ? Block{b.c0, b.j + 1u} : Block{b.c0 + chunk, 0u}; };
+    auto first = [&](Block b) { return b.c0 + b.j * kBK; };
+    auto end = [&](Block b) { return (uint32_t)min(kend, b.c0 + chunk); };
+    uint4 sa[kAhead][CA], sb[kAhead][CB];
+    const uint32_t ra0 = tid / (BM / 8u), rb0 = tid / (BN / 8u);  // rows of the thread's first chunks
+    constexpr uint32_t kStepA = 256u / (BM / 8u), kStepB = 256u / (BN / 8u);
+    const uint32_t ca = 8u * (tid % (BM / 8u)), cb = 8u * (tid % (BN / 8u));
+    const uint32_t oa = 2u * (ra0 * lda + min(ca, lda - 8u - m0)), ob = 2u * (rb0 * ldb + min(cb, ldb - 8u - n0));
+    const uint32_t klast = kbeg + (kend - 1u - kbeg) / chunk * chunk;  // the last chunk's first row ...
+    const uint32_t kclamp = klast + (kend - 1u - klast) / kBK * kBK;   // ... and its last block's
+    auto fetch = [&](Block b, uint4 (&ra)[CA], uint4 (&rb)[CB]) {
+        const uint32_t k0 = min(first(b), kclamp);
+        const uint16_t *pa = A + (size_t)k0 * lda + m0, *pb = B + (size_t)k0 * ldb + n0;
+#pragma unroll
+        for (uint32_t c = 0; c < CA; ++c) ra[c] = ld8u(pa + (size_t)(kStepA * c) * lda, oa);
+#pragma unroll
+        for (uint32_t c = 0; c < CB; ++c) rb[c] = ld8u(pb + (size_t)(kStepB * c) * ldb, ob);
+    };
+    auto store = [&](uint32_t buf, uint32_t k0, uint32_t ce, const uint4 (&ra)[CA], const uint4 (&rb)[CB], auto whole) {
+        constexpr bool kWhole = decltype(whole)::value;
+        uint16_t *la = sA + buf * kTA + ra0 * kLdA + ca, *lb = sB + buf * kTB + rb0 * kLdB + cb;
+#pragma unroll
+        for (uint32_t c = 0; c < CA; ++c)
+            *reinterpret_cast<uint4 *>(la + kStepA * c * kLdA) = keep(kWhole || k0 + ra0 + kStepA * c < ce, ra[c]);
+#pragma unroll
+        for (uint32_t c = 0; c < CB; ++c)
+            *reinterpret_cast<uint4 *>(lb + kStepB * c * kLdB) = keep(kWhole || k0 + rb0 + kStepB * c < ce, rb[c]);
+    };
+    auto stage = [&](uint32_t buf, Block b, const uint4 (&ra)[CA], const uint4 (&rb)[CB]) {
+        const uint32_t k0 = first(b), ce = end(b);
+        if (k0 + kBK <= ce) store(buf, k0, ce, ra, rb, std::true_type{});
+        else store(buf, k0, ce, ra, rb, std::false_type{});
+    };
+    const v16f zero = {};
+    v16f acc[MI][NI], tot[MI][NI], accb[NI], totb[NI];
+#pragma unroll
+    for (uint32_t j = 0; j < NI; ++j) {
+        accb[j] = totb[j] = zero;
+#pragma unroll
+        for (uint32_t i = 0; i < MI; ++i) acc[i][j] = tot[i][j] = zero;
+    }
+    v8bf ones;
+#pragma unroll
+    for (uint32_t t = 0; t < 8u; ++t) ones[t] = (__bf16)1.0f;
+    Block cur{kbeg, 0u}, ahead = cur;  // the block computed, the next to fetch
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u) {
+        fetch(ahead, sa[u], sb[u]);
+        ahead = next(ahead);
+    }
+    stage(0, cur, sa[0], sb[0]);
+    __syncthreads();
+    uint32_t buf = 0;
+    while (first(cur) < kend) {  // (kAhead blocks a turn; those past the end are zero)
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u) {
+            fetch(ahead, sa[u], sb[u]);
+            ahead = next(ahead);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint16_t *ta = sA + buf * kTA, *tb = sB + buf * kTB;
+            constexpr uint32_t NK = kBK / 16u;
+            v8bf fa[NK][MI], fb[NK][NI];
+#pragma unroll
+            for (uint32_t q = 0; q < NK; ++q) {
+#pragma unroll
+                for (uint32_t i = 0; i < MI; ++i) fa[q][i] = frag<32, true>(ta, kLdA, (wm * MI + i) * 32u, 16u * q, lane);
+#pragma unroll
+                for (uint32_t j = 0; j < NI; ++j) fb[q][j] = frag<32, true>(tb, kLdB, (wn * NI + j) * 32u, 16u * q, lane);
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < NK; ++q)
+#pragma unroll
+                for (uint32_t i = 0; i < MI; ++i)
+#pragma unroll
+                    for (uint32_t j = 0; j < NI; ++j) acc[i][j] = Mfma<32>::mac(fa[q][i], fb[q][j], acc[i][j]);
+            if (bias) {
+#pragma unroll
+                for (uint32_t q = 0; q < NK; ++q)
+#pragma unroll
+                    for (uint32_t j = 0; j < NI; ++j) accb[j] = Mfma<32>::mac(ones, fb[q][j], accb[j]);
+            }
+            const Block after = next(cur);
+            if (after.j == 0u) {  // the chunk's last block
+#pragma unroll
+                for (uint32_t j = 0; j < NI; ++j) {
+                    totb[j] += accb[j];
+                    accb[j] = zero;
+#pragma unroll
+                    for (uint32_t i = 0; i < MI; ++i) {
+                        tot[i][j] += acc[i][j];
+                        acc[i][j] = zero;
+                    }
+                }
+            }
+            stage(buf ^ 1u, after, sa[(u + 1u) % kAhead], sb[(u + 1u) % kAhead]);
+            __syncthreads();
+            buf ^= 1u;
+            cur = after;
+        }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < NI; ++j) {
+        const uint32_t n = n0 + (wn * NI + j) * 32u + (lane & 31u);
+        if (n >= N) continue;
+#pragma unroll
+        for (uint32_t i = 0; i < MI; ++i)
+#pragma unroll
+            for (uint32_t t = 0; t < 16u; ++t) {
+                const uint32_t m = m0 + (wm * MI + i) * 32u + Mfma<32>::row(t, lane);
+                if (m < M) out[(size_t)m * N + n] = tot[i][j][t] + acc[i][j][t];
+            }
+        if (bias && lane < 32u) out[(size_t)M * N + n] = totb[j][0] + accb[j][0];
+    }
+}
+
+__global__ void __launch_bounds__(256) mlp_grad(const GradArgs g)
+{
+    constexpr uint32_t kLds2 = 4u * kBK * (64u + kPadK), kLds3 = 2u * kBK * (128u + kPadK + 32u + kPadK);
+    __shared__ __align__(16) uint16_t lds[kLds2 > kLds3 ? kLds2 : kLds3];
+    const uint32_t ntiles = g.tiles1 + g.tiles2 + g.tiles3;
+    const uint32_t job = xcd_tile(blockIdx.x, gridDim.x);
+    const uint32_t part = job / ntiles;
+    uint32_t tile = job % ntiles;
+    const uint32_t kbeg = part * g.chunk, kend = g.parts > 1u ? min(g.batch, kbeg + g.chunk) : g.batch;
+    const size_t off = part * g.stride;
+    if (tile < g.tiles2) {
+        const uint32_t tn = (g.H + 63u) / 64u;
+        grad_tile<64, 64, 2>(lds, g.h1, g.dz2, g.H, g.H, g.H, g.H, tile / tn * 64u, tile % tn * 64u, kbeg, kend,
+                                         g.chunk, g.o2 + off);
+    } else if ((tile -= g.tiles2) < g.tiles1) {
+        grad_tile<64, 64, 2>(lds, g.x, g.dz1, (g.din + 15u) & ~15u, g.H, g.din, g.H, 0u, tile * 64u, kbeg, kend, g.chunk,
+                                          g.o1 + off);
+    } else {
+        tile -= g.tiles1;
+        grad_tile<128, 32, 4>(lds, g.h2, g.dy, g.H, 16u, g.H, g.dout, tile * 128u, 0u, kbeg, kend, g.chunk,
+                                           g.o3 + off);
+    }
+}
+
+// The chunks' results added in chunk order (n parameters, the parameter layout).
+__global__ void __launch_bounds__(256) grad_reduce(const float *part, uint32_t parts, size_t stride, uint64_t n,
+                                                   float *grads)
+{
+    const uint64_t e = ((uint64_t)blockIdx.x * 256u + threadIdx.x) * 4u;
+    if (e >= n) return;
+    if (e + 4u <= n) {
+        v4f s = *reinterpret_cast<const v4f_any *>(part + e);
+#pragma unroll 4
+        for (uint32_t p = 1; p < parts; ++p) s += *reinterpret_cast<const v4f_any *>(part + p * stride + e);
+        *reinterpret_cast<v4f_any *>(grads + e) = s;
+    } else {
+        for (uint64_t i = e; i < n; ++i) {
+            float s = part[i];
+            for (uint32_t p = 1; p < parts; ++p) s += part[p * stride + i];
+            grads[i] = s;
         }
     }
 }
 
-// out[i] = sum over the `parts` split-K partial results, in partial order (deterministic).
-__global__ void sum_partials(const float *part, uint32_t parts, uint64_t n, float *out)
-{
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-        float s = 0.f;
-        for (uint32_t p = 0; p < parts; ++p) s += part[(size_t)p * n + i];
-        out[i] = s;
-    }
-}
-
-__global__ void to_bf16(const float *x, uint16_t *y, uint64_t n)
-{
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        y[i] = f2bf(x[i]);
-}
-
-// Mean loss over n values and its gradient, one workgroup, fixed reduction order.
+// Mean loss over n values and its gradient, r = y - t:
 //   kind 0 (squared error): loss = mean r^2,                         dy = 2 r / n
 //   kind 1 (Huber, delta):  loss = mean(r^2/2 if |r| <= delta else delta (|r| - delta/2)),
 //                           dy = clamp(r, -delta, delta) / n
-// with r = y - t.
-__global__ void __launch_bounds__(1024) loss_grad(const float *y, const float *t, float *dy, float *loss, uint32_t n,
-                                                  int kind, float delta)
+// Workgroup 0 sums the loss, one strided chain per thread and then a tree over the threads (a
+// fixed order whatever the grid), kLossAhead of a chain's values in flight; the other workgroups write
+// the gradient, or workgroup 0 does when it is alone.
+constexpr uint32_t kLossThreads = 1024, kLossAhead = 32;
+
+__global__ void __launch_bounds__(kLossThreads) loss_grad(const float *y, const float *t, float *dy, float *loss,
+                                                          uint32_t n, int kind, float delta)
 {
-    __shared__ float part[1024];
-    float s = 0.f;
+    __shared__ float part[kLossThreads];
     const float inv = 1.0f / (float)n;
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const float d = y[i] - t[i];
-        if (kind == 0) {
-            dy[i] = 2.0f * d * inv;
-            s += d * d;
-        } else {
-            const float a = fabsf(d);
-            dy[i] = fminf(fmaxf(d, -delta), delta) * inv;
-            s += a <= delta ? 0.5f * d * d : delta * (a - 0.5f * delta);
+    auto grad = [&](float d) { return kind == 0 ? 2.0f * d * inv : fminf(fmaxf(d, -delta), delta) * inv; };
+    if (blockIdx.x > 0u) {
+        const uint64_t step = (uint64_t)(gridDim.x - 1u) * kLossThreads;
+        for (uint64_t i = (uint64_t)(blockIdx.x - 1u) * kLossThreads + threadIdx.x; i < n; i += step)
+            dy[i] = grad(y[i] - t[i]);
+        return;
+    }
+    const bool alone = gridDim.x == 1u;
+    float s = 0.f;
+    for (uint64_t i0 = threadIdx.x; i0 < n; i0 += (uint64_t)kLossAhead * kLossThreads) {
+        float d[kLossAhead];
+#pragma unroll
+        for (uint32_t u = 0; u < kLossAhead; ++u) {
+            const uint64_t i = i0 + u * kLossThreads;
+            const uint64_t c = i < n ? i : n - 1u;
+            d[u] = y[c] - t[c];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kLossAhead; ++u) {
+            const uint64_t i = i0 + u * kLossThreads;
+            if (i >= n) continue;
+            if (alone) dy[i] = grad(d[u]);
+            const float a = fabsf(d[u]);
+            s += kind == 0 ? d[u] * d[u] : (a <= delta ? 0.5f * d[u] * d[u] : delta * (a - 0.5f * delta));
         }
     }
     part[threadIdx.x] = s;
     __syncthreads();
-    for (uint32_t w = blockDim.x / 2; w > 0; w >>= 1) {
+    for (uint32_t w = kLossThreads / 2; w > 0; w >>= 1) {
         if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
         __syncthreads();
     }
@@ -192,37 +699,106 @@ __host__ __device__ inline Layout layout(uint32_t din, uint32_t H, uint32_t dout
 }
 
 // Adam (Kingma and Ba 2015, algorithm 1) on the fp32 parameters; weights also refresh their
-// bfloat16 copies.  c1 = 1 - beta1^t, c2 = 1 - beta2^t.
-__global__ void adam_step(float *p, const float *g, float *m, float *v, uint16_t *wb, Layout l, float lr,
-                          float beta1, float beta2, float eps, float c1, float c2, int update)
+// bfloat16 copies.  c1 = 1 - beta1^t, c2 = 1 - beta2^t; update 0 only rewrites the copies.
+struct AdamArgs {
+    float *p;
+    const float *g;
+    float *m, *v;
+    uint16_t *wb;
+    Layout l;
+    uint32_t H, tiles;  // tiles of 64 along a side of W2
+    float lr, beta1, beta2, eps, c1, c2;
+    int update;
+};
+
+__device__ __forceinline__ float adam_value(const AdamArgs &a, float p, float g, float &m, float &v)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < l.P; i += (uint64_t)gridDim.x * blockDim.x) {
-        float pi = p[i];
-        if (update) {
-            const float gi = g[i];
-            const float mi = beta1 * m[i] + (1.0f - beta1) * gi;
-            const float vi = beta2 * v[i] + (1.0f - beta2) * gi * gi;
-            m[i] = mi;
-            v[i] = vi;
-            pi -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-            p[i] = pi;
+    m = a.beta1 * m + (1.0f - a.beta1) * g;
+    v = a.beta2 * v + (1.0f - a.beta2) * g * g;
+    return p - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+}
+
+// The first tiles^2 workgroups each take 64 x 64 of W2 (four parameters per access; the transposed
+// copy goes through LDS so that both copies are written in rows), the others the remaining
+// parameters one by one.  Bound by the 28 bytes per parameter it reads and writes.
+__global__ void __launch_bounds__(256) adam_step(const AdamArgs a)
+{
+    constexpr uint32_t kLd = 72;
+    __shared__ __align__(16) uint16_t t[64 * kLd];
+    const uint32_t tid = threadIdx.x, H = a.H;
+    if (blockIdx.x < a.tiles * a.tiles) {
+        const uint32_t k0 = blockIdx.x / a.tiles * 64u, n0 = blockIdx.x % a.tiles * 64u;
+        const uint32_t n = n0 + 4u * (tid & 15u), r = tid >> 4;
+        v4f p[4], g[4], m[4], v[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+            const uint32_t k = k0 + r + 16u * j;
+            if (k < H && n < H) {  // H is a multiple of 16
+                const size_t i = a.l.w2 + (size_t)k * H + n;
+                p[j] = *reinterpret_cast<const v4f_any *>(a.p + i);
+                if (a.update) {
+                    g[j] = *reinterpret_cast<const v4f_any *>(a.g + i);
+                    m[j] = *reinterpret_cast<const v4f_any *>(a.m + i);
+                    v[j] = *reinterpret_cast<const v4f_any *>(a.v + i);
+                }
+            }
         }
-        int64_t w = -1;  // index in the bf16 copies
-        if (i < l.b1) w = (int64_t)i;
-        else if (i >= l.w2 && i < l.b2) w = (int64_t)(l.b1 + (i - l.w2));
-        else if (i >= l.w3 && i < l.b3) w = (int64_t)(l.b1 + (l.b2 - l.w2) + (i - l.w3));
-        if (w >= 0) wb[w] = f2bf(pi);
-        if (i >= l.w2 && i < l.b2) {  // W2[k][n] -> W2T[n][k]
-            const uint64_t H = l.w3 - l.b2;
-            const uint64_t k = (i - l.w2) / H, n = (i - l.w2) % H;
-            wb[l.w2t + n * H + k] = f2bf(pi);
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+            const uint32_t k = k0 + r + 16u * j;
+            if (k < H && n < H) {
+                const size_t i = a.l.w2 + (size_t)k * H + n;
+                if (a.update) {
+#pragma unroll
+                    for (uint32_t c = 0; c < 4u; ++c) {
+                        float mc = m[j][c], vc = v[j][c];
+                        p[j][c] = adam_value(a, p[j][c], g[j][c], mc, vc);
+                        m[j][c] = mc;
+                        v[j][c] = vc;
+                    }
+                    *reinterpret_cast<v4f_any *>(a.m + i) = m[j];
+                    *reinterpret_cast<v4f_any *>(a.v + i) = v[j];
+                    *reinterpret_cast<v4f_any *>(a.p + i) = p[j];
+                }
+                uint16_t b[4];
+#pragma unroll
+                for (uint32_t c = 0; c < 4u; ++c) {
+                    b[c] = f2bf(p[j][c]);
+                    t[(4u * (tid & 15u) + c) * kLd + r + 16u * j] = b[c];
+                }
+                *reinterpret_cast<v2u_any *>(a.wb + a.l.b1 + (size_t)k * H + n) =
+                    v2u_any{(uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16)};
+            }
         }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t j = 0; j < 2u; ++j) {  // W2T[n][k]: rows of 64, eight per access
+            const uint32_t e = tid + 256u * j, nl = e >> 3, kl = 8u * (e & 7u);
+            if (n0 + nl < H && k0 + kl < H) {
+                const uint4 w = *reinterpret_cast<const uint4 *>(t + nl * kLd + kl);
+                *reinterpret_cast<v4u_any *>(a.wb + a.l.w2t + (size_t)(n0 + nl) * H + k0 + kl) = v4u_any{w.x, w.y, w.z, w.w};
+            }
+        }
+        return;
     }
+    const uint64_t e = (uint64_t)(blockIdx.x - a.tiles * a.tiles) * 256u + tid;
+    const uint64_t i = e < a.l.w2 ? e : e + (a.l.b2 - a.l.w2);  // W1 b1, then b2 W3 b3
+    if (i >= a.l.P) return;
+    float pi = a.p[i];
+    if (a.update) {
+        float mi = a.m[i], vi = a.v[i];
+        pi = adam_value(a, pi, a.g[i], mi, vi);
+        a.m[i] = mi;
+        a.v[i] = vi;
+        a.p[i] = pi;
+    }
+    if (i < a.l.b1) a.wb[i] = f2bf(pi);
+    else if (i >= a.l.w3 && i < a.l.b3) a.wb[a.l.b1 + (a.l.b2 - a.l.w2) + (i - a.l.w3)] = f2bf(pi);
 }
 
 // Inference of the whole network for kPredRows rows per workgroup (four waves), in one launch.
 // The input tile and both hidden activations stay in LDS (bf16, rows padded by 8 elements);
-// the layer products use the same MFMA tiles, k order and rounding points as mlp_gemm, so the
+// the layer products use the same MFMA tiles, k order and rounding points as mlp_layer, so the
 // outputs equal cae_mlp_forward's bit for bit.
 constexpr uint32_t kPredRows = 32;
 constexpr uint32_t kPredPad = 8;
@@ -366,8 +942,6 @@ __global__ void __launch_bounds__(256) mlp_predict(const PredArgs a)
 // Rounding points and fp32 accumulation are those of the unfused kernels; only the order of the
 // fp32 sums differs.
 // ------------------------------------------------------------------------------------------
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-
 constexpr uint32_t kTrainRows = 16;
 constexpr uint32_t kRowWaves = 16;   // waves of an mlp_train_rows workgroup: one 16-column tile each at H = 256
 constexpr uint32_t kParamSplit = 4;  // waves that reduce one weight-gradient tile, each a quarter of the batch
@@ -377,11 +951,6 @@ constexpr uint32_t kLoadAhead = 8;
 constexpr uint32_t kTrainMaxH = 256;
 constexpr uint32_t kTrainMaxIn = 32;
 constexpr uint32_t kTrainPad = 8;  // bf16 elements of padding per LDS row
-
-__device__ __forceinline__ v8bf ld8(const uint16_t *p)  // eight bfloat16, 16-byte aligned
-{
-    return __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(p));
-}
 
 __device__ __forceinline__ v8bf pack8(const uint16_t (&e)[8])
 {
@@ -692,6 +1261,7 @@ __global__ void __launch_bounds__(kParamSplit * 64) mlp_train_params(const Train
 
 namespace {
 int forward_impl(const cae_mlp *net, const float *x, float *y, uint32_t N, void *ws, hipStream_t s);
+int backward_impl(const cae_mlp *net, const float *dy, float *grads, uint32_t N, void *ws, hipStream_t s);
 }  // namespace
 
 namespace cae_detail {
@@ -702,30 +1272,60 @@ namespace {
 
 int mfail(int code, const char *msg) { return cae_detail::set_error(code, msg); }
 
+// Workspace of the layer-by-layer path: activations and pre-activations of the forward pass,
+// back-propagated gradients and the weight gradients' split-batch parts.
 struct WsLayout {
     size_t xb, z1, h1, z2, h2, dyb, dz2, dz1, part, total;
 };
 
-constexpr uint32_t kSplitChunk = 256;  // batch rows per split-K part of a weight gradient
-constexpr uint32_t kMaxParts = 64;
+// The bfloat16 arrays end in a block of rows that may be read (its values are never used).
+constexpr uint64_t kPadRows = kBK;
 
 size_t al(size_t x) { return (x + 255) / 256 * 256; }
+
+// Chunks of the batch in the weight gradients (kSplitChunk rows, more beyond kMaxParts of them),
+// and whether each is a workgroup of its own.  The chunks' results then cross memory twice, so
+// tiles that already fill the chip take every chunk themselves.
+constexpr uint32_t kSplitChunk = 256;
+constexpr uint32_t kMaxParts = 64;
+constexpr uint32_t kGradTiles = 128;  // tiles of W2 from which a workgroup takes all chunks
+
+struct GradSplit {
+    uint32_t tiles1, tiles2, tiles3, parts, chunk;
+};
+
+GradSplit grad_split(uint32_t H, uint32_t N)
+{
+    GradSplit s;
+    const uint32_t t = (H + 63u) / 64u;
+    s.tiles1 = t;
+    s.tiles2 = t * t;
+    s.tiles3 = (H + 127u) / 128u;
+    const uint32_t chunks = (uint32_t)std::min<uint64_t>(kMaxParts, ((uint64_t)N + kSplitChunk - 1u) / kSplitChunk);
+    s.chunk = (uint32_t)(((uint64_t)N + chunks - 1u) / chunks + 15u) / 16u * 16u;
+    s.parts = s.tiles2 >= kGradTiles ? 1u : (uint32_t)(((uint64_t)N + s.chunk - 1u) / s.chunk);
+    return s;
+}
+
+size_t part_stride(uint64_t P) { return (size_t)(P + 3u) / 4u * 4u; }  // floats per part, 16-byte steps
 
 WsLayout ws_layout(uint32_t din, uint32_t H, uint32_t dout, uint32_t N)
 {
     WsLayout w;
     size_t o = 0;
-    w.xb = o; o = al(o + 2ull * N * din);
+    w.xb = o; o = al(o + 2ull * (N + kPadRows) * ((din + 15u) & ~15u));
     w.z1 = o; o = al(o + 4ull * N * H);
-    w.h1 = o; o = al(o + 2ull * N * H);
+    w.h1 = o; o = al(o + 2ull * (N + kPadRows) * H);
     w.z2 = o; o = al(o + 4ull * N * H);
-    w.h2 = o; o = al(o + 2ull * N * H);
-    w.dyb = o; o = al(o + 2ull * N * dout);
-    w.dz2 = o; o = al(o + 2ull * N * H);
-    w.dz1 = o; o = al(o + 2ull * N * H);
-    const uint64_t parts = std::min<uint64_t>(kMaxParts, (N + kSplitChunk - 1) / kSplitChunk);
-    const uint64_t rows = std::max<uint64_t>(din, H) + 1;
-    w.part = o; o = al(o + 4ull * parts * rows * std::max<uint32_t>(H, dout));
+    w.h2 = o; o = al(o + 2ull * (N + kPadRows) * H);
+    w.dyb = o; o = al(o + 2ull * (N + kPadRows) * 16u);
+    w.dz2 = o; o = al(o + 2ull * (N + kPadRows) * H);
+    w.dz1 = o; o = al(o + 2ull * (N + kPadRows) * H);
+    // parts grow with the batch, so a workspace for N holds every smaller batch's
+    const size_t parts = grad_split(H, std::max(N, 1u)).tiles2 >= kGradTiles
+                             ? 0u
+                             : std::min<size_t>(kMaxParts, ((size_t)N + kSplitChunk - 1u) / kSplitChunk);
+    w.part = o; o = al(o + 4ull * parts * part_stride(layout(din, H, dout).P));
     w.total = o;
     return w;
 }
@@ -762,60 +1362,34 @@ int check_net(const cae_mlp *net)
     return CAE_OK;
 }
 
-template <bool TA, bool TB, int EPI>
-void gemm(GemmArgs g, hipStream_t s)
-{
-    if (g.kchunk == 0) g.kchunk = g.K;
-    const uint32_t tiles = ((g.M + g.ones_row + 15u) / 16u) * ((g.N + 15u) / 16u);
-    hipLaunchKernelGGL((mlp_gemm<TA, TB, EPI>), dim3((tiles + 3u) / 4u), dim3(256), 0, s, g);
-}
-
-// Weight gradient [M+1][N] = [A^T ; 1^T] B over the batch (the last row is the bias gradient),
-// split over batch chunks into partials and summed in chunk order.
-void weight_grad(const uint16_t *A, uint32_t lda, const uint16_t *B, uint32_t ldb, uint32_t M, uint32_t N,
-                 uint32_t batch, float *out, float *part, hipStream_t s)
-{
-    GemmArgs g{};
-    g.A = A;
-    g.B = B;
-    g.lda = lda;
-    g.ldb = ldb;
-    g.M = M;
-    g.N = N;
-    g.K = batch;
-    g.ones_row = 1;
-    g.ldo = N;
-    const uint32_t parts = std::min<uint32_t>(kMaxParts, (batch + kSplitChunk - 1) / kSplitChunk);
-    g.kchunk = ((batch + parts - 1) / parts + 15u) / 16u * 16u;
-    const uint32_t nparts = (batch + g.kchunk - 1) / g.kchunk;
-    g.Of = nparts > 1 ? part : out;
-    const uint32_t tiles = ((M + 1 + 15u) / 16u) * ((N + 15u) / 16u);
-    hipLaunchKernelGGL((mlp_gemm<true, false, EPI_F32>), dim3((tiles + 3u) / 4u, nparts), dim3(256), 0, s, g);
-    if (nparts > 1) {
-        const uint64_t n = (uint64_t)(M + 1) * N;
-        hipLaunchKernelGGL(sum_partials, dim3((uint32_t)std::min<uint64_t>((n + 255) / 256, 1024)), dim3(256), 0, s,
-                           part, nparts, n, out);
-    }
-}
-
-GemmArgs gargs(const uint16_t *A, uint32_t lda, const uint16_t *B, uint32_t ldb, uint32_t M, uint32_t N, uint32_t K)
-{
-    GemmArgs g{};
-    g.A = A;
-    g.B = B;
-    g.lda = lda;
-    g.ldb = ldb;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    return g;
-}
-
 int launch_status()
 {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return mfail(CAE_EHIP, hipGetErrorString(e));
     return CAE_OK;
+}
+
+void launch_adam(const cae_mlp *net, const float *g, float *m, float *v, float lr, float beta1, float beta2,
+                 float eps, float c1, float c2, int update, hipStream_t s)
+{
+    AdamArgs a;
+    a.p = net->params;
+    a.g = g;
+    a.m = m;
+    a.v = v;
+    a.wb = net->weights;
+    a.l = layout(net->d_in, net->d_hidden, net->d_out);
+    a.H = net->d_hidden;
+    a.tiles = (a.H + 63u) / 64u;
+    a.lr = lr;
+    a.beta1 = beta1;
+    a.beta2 = beta2;
+    a.eps = eps;
+    a.c1 = c1;
+    a.c2 = c2;
+    a.update = update;
+    const uint32_t rest = (uint32_t)((a.l.P - (a.l.b2 - a.l.w2) + 255u) / 256u);
+    hipLaunchKernelGGL(adam_step, dim3(a.tiles * a.tiles + rest), dim3(256), 0, s, a);
 }
 
 // Scratch of cae_mlp_train_step_noalloc: the fused training step's workspace (transposed
@@ -946,9 +1520,7 @@ int cae_mlp_refresh_weights(const cae_mlp *net, void *stream)
 {
     int rc = check_net(net);
     if (rc) return rc;
-    const Layout l = layout(net->d_in, net->d_hidden, net->d_out);
-    hipLaunchKernelGGL(adam_step, dim3(256), dim3(256), 0, (hipStream_t)stream, net->params, nullptr, nullptr,
-                       nullptr, net->weights, l, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f, 0);
+    launch_adam(net, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f, 0, (hipStream_t)stream);
     return launch_status();
 }
 
@@ -996,42 +1568,8 @@ int cae_mlp_backward(const cae_mlp *net, const float *x, const float *dy, float 
     int rc = check_net(net);
     if (rc) return rc;
     if (!dy || !grads || !ws) return mfail(CAE_EINVAL, "NULL dy, grads or workspace");
-    hipStream_t s = (hipStream_t)stream;
-    const uint32_t din = net->d_in, H = net->d_hidden, dout = net->d_out;
-    const Layout l = layout(din, H, dout);
-    const WsLayout w = ws_layout(din, H, dout, N);
-    unsigned char *b = static_cast<unsigned char *>(ws);
-    const uint16_t *xb = reinterpret_cast<const uint16_t *>(b + w.xb);
-    const float *z1 = reinterpret_cast<const float *>(b + w.z1);
-    const uint16_t *h1 = reinterpret_cast<const uint16_t *>(b + w.h1);
-    const float *z2 = reinterpret_cast<const float *>(b + w.z2);
-    const uint16_t *h2 = reinterpret_cast<const uint16_t *>(b + w.h2);
-    uint16_t *dyb = reinterpret_cast<uint16_t *>(b + w.dyb);
-    uint16_t *dz2 = reinterpret_cast<uint16_t *>(b + w.dz2);
-    uint16_t *dz1 = reinterpret_cast<uint16_t *>(b + w.dz1);
-    float *part = reinterpret_cast<float *>(b + w.part);
-    const uint16_t *W1 = net->weights, *W2 = W1 + (size_t)din * H, *W3 = W2 + (size_t)H * H;
-    (void)W1;
     if (N == 0) return mfail(CAE_EINVAL, "backward needs N >= 1");
-    const uint64_t ny = (uint64_t)N * dout;
-    hipLaunchKernelGGL(to_bf16, dim3((uint32_t)std::min<uint64_t>((ny + 255) / 256, 1024)), dim3(256), 0, s, dy, dyb, ny);
-    // output layer: [dW3; db3] = [h2; 1]^T dy (b3 directly follows W3 in the layout)
-    weight_grad(h2, H, dyb, dout, H, dout, N, grads + l.w3, part, s);
-    // dz2 = (dy W3^T) * silu'(z2)
-    GemmArgs g = gargs(dyb, dout, W3, dout, N, H, dout);
-    g.Zin = z2;
-    g.Ob = dz2;
-    g.ldo = H;
-    gemm<false, true, EPI_DSILU>(g, s);
-    weight_grad(h1, H, dz2, H, H, H, N, grads + l.w2, part, s);
-    // dz1 = (dz2 W2^T) * silu'(z1)
-    g = gargs(dz2, H, W2, H, N, H, H);
-    g.Zin = z1;
-    g.Ob = dz1;
-    g.ldo = H;
-    gemm<false, true, EPI_DSILU>(g, s);
-    weight_grad(xb, din, dz1, H, din, H, N, grads + l.w1, part, s);
-    return launch_status();
+    return backward_impl(net, dy, grads, N, ws, (hipStream_t)stream);
 }
 
 int cae_mlp_adam(const cae_mlp *net, const float *grads, float *m, float *v, uint32_t step, float lr, float beta1,
@@ -1041,11 +1579,9 @@ int cae_mlp_adam(const cae_mlp *net, const float *grads, float *m, float *v, uin
     if (rc) return rc;
     if (!grads || !m || !v) return mfail(CAE_EINVAL, "NULL grads or moments");
     if (step < 1) return mfail(CAE_EINVAL, "step counts from 1");
-    const Layout l = layout(net->d_in, net->d_hidden, net->d_out);
     const float c1 = (float)(1.0 - std::pow((double)beta1, (double)step));
     const float c2 = (float)(1.0 - std::pow((double)beta2, (double)step));
-    hipLaunchKernelGGL(adam_step, dim3((uint32_t)std::min<uint64_t>((l.P + 255) / 256, 1024)), dim3(256), 0,
-                       (hipStream_t)stream, net->params, grads, m, v, net->weights, l, lr, beta1, beta2, eps, c1, c2, 1);
+    launch_adam(net, grads, m, v, lr, beta1, beta2, eps, c1, c2, 1, (hipStream_t)stream);
     return launch_status();
 }
 
@@ -1088,7 +1624,16 @@ int cae_mlp_loss_grad(const float *y, const float *target, float *dy, float *los
     if (n == 0) return mfail(CAE_EINVAL, "n must be >= 1");
     if (kind != CAE_LOSS_MSE && kind != CAE_LOSS_HUBER) return mfail(CAE_EINVAL, "unknown loss kind");
     if (kind == CAE_LOSS_HUBER && !(delta > 0.0f)) return mfail(CAE_EINVAL, "Huber delta must be > 0");
-    hipLaunchKernelGGL(loss_grad, dim3(1), dim3(1024), 0, (hipStream_t)stream, y, target, dy, loss, n, kind, delta);
+    // the gradient in workgroups of its own, unless it is short or overwrites an input that
+    // workgroup 0 may still read
+    const auto apart = [n](const void *a, const void *b, size_t nb) {
+        const uintptr_t x = reinterpret_cast<uintptr_t>(a), z = reinterpret_cast<uintptr_t>(b);
+        return x + 4u * (size_t)n <= z || z + nb <= x;
+    };
+    const bool split = n > 2u * kLossThreads && apart(dy, y, 4u * (size_t)n) && apart(dy, target, 4u * (size_t)n);
+    const uint32_t blocks = split ? 1u + std::min<uint32_t>((n + kLossThreads - 1u) / kLossThreads, 512u) : 1u;
+    hipLaunchKernelGGL(loss_grad, dim3(blocks), dim3(kLossThreads), 0, (hipStream_t)stream, y, target, dy, loss, n,
+                       kind, delta);
     return launch_status();
 }
 
@@ -1096,41 +1641,118 @@ int cae_mlp_loss_grad(const float *y, const float *target, float *dy, float *los
 
 namespace {
 
-// The unfused forward pass: x -> bf16, then three matrix-core layer products, activations kept in
-// ws (the prefix of ws_layout) for cae_mlp_backward.
+constexpr uint32_t kLayerBlocks = 256;  // workgroups that fill the chip
+
+// Launches one layer product in the widest workgroup tile that gives every CU a workgroup: at
+// 4096 x 1024 x 1024 tiles of 128 x 64 take 21.5 us, 64 x 64 22.4, 128 x 128 (one workgroup of four
+// waves per CU) 22.9.  Short products spend their time in the epilogue and take 64 x 64 at most.
+template <bool AF32, bool KMAJOR, int EPI>
+void layer(const LayerArgs &g, hipStream_t s)
+{
+    auto blocks = [&](uint32_t bm, uint32_t bn) { return ((g.M + bm - 1u) / bm) * ((g.N + bn - 1u) / bn); };
+    const dim3 block(256);
+    if constexpr (!AF32) {
+        if (blocks(128u, 64u) >= kLayerBlocks) {
+            hipLaunchKernelGGL((mlp_layer<64, 32, AF32, KMAJOR, EPI>), dim3(blocks(128u, 64u)), block, 0, s, g);
+            return;
+        }
+    }
+    if (blocks(64u, 64u) >= kLayerBlocks)
+        hipLaunchKernelGGL((mlp_layer<32, 32, AF32, KMAJOR, EPI>), dim3(blocks(64u, 64u)), block, 0, s, g);
+    else
+        hipLaunchKernelGGL((mlp_layer<16, 16, AF32, KMAJOR, EPI>), dim3(blocks(32u, 32u)), block, 0, s, g);
+}
+
+// The layer-by-layer forward pass: activations and pre-activations are kept in ws for
+// backward_impl.
 int forward_impl(const cae_mlp *net, const float *x, float *y, uint32_t N, void *ws, hipStream_t s)
 {
     const uint32_t din = net->d_in, H = net->d_hidden, dout = net->d_out;
     const Layout l = layout(din, H, dout);
     const WsLayout w = ws_layout(din, H, dout, N);
     unsigned char *b = static_cast<unsigned char *>(ws);
-    uint16_t *xb = reinterpret_cast<uint16_t *>(b + w.xb);
-    float *z1 = reinterpret_cast<float *>(b + w.z1);
-    uint16_t *h1 = reinterpret_cast<uint16_t *>(b + w.h1);
-    float *z2 = reinterpret_cast<float *>(b + w.z2);
-    uint16_t *h2 = reinterpret_cast<uint16_t *>(b + w.h2);
     const uint16_t *W1 = net->weights, *W2 = W1 + (size_t)din * H, *W3 = W2 + (size_t)H * H;
-    const uint64_t nx = (uint64_t)N * din;
-    hipLaunchKernelGGL(to_bf16, dim3((uint32_t)std::min<uint64_t>((nx + 255) / 256, 1024)), dim3(256), 0, s, x, xb, nx);
-    GemmArgs g = gargs(xb, din, W1, H, N, H, din);
+    LayerArgs g{};
+    g.Af = x;
+    g.Acopy = reinterpret_cast<uint16_t *>(b + w.xb);
+    g.ldc = (din + 15u) & ~15u;
+    g.B = W1;
+    g.M = N;
+    g.N = H;
+    g.K = din;
     g.bias = net->params + l.b1;
-    g.Of = z1;
-    g.Ob = h1;
-    g.ldo = H;
-    gemm<false, false, EPI_HIDDEN>(g, s);
-    g = gargs(h1, H, W2, H, N, H, H);
+    g.Z = reinterpret_cast<float *>(b + w.z1);
+    g.O = reinterpret_cast<uint16_t *>(b + w.h1);
+    layer<true, true, EPI_HIDDEN>(g, s);
+    g.A = g.O;
+    g.B = W2;
+    g.K = H;
     g.bias = net->params + l.b2;
-    g.Of = z2;
-    g.Ob = h2;
-    g.ldo = H;
-    gemm<false, false, EPI_HIDDEN>(g, s);
-    g = gargs(h2, H, W3, dout, N, dout, H);
-    g.bias = net->params + l.b3;
-    g.Of = y;
-    g.ldo = dout;
-    gemm<false, false, EPI_OUTPUT>(g, s);
+    g.Z = reinterpret_cast<float *>(b + w.z2);
+    g.O = reinterpret_cast<uint16_t *>(b + w.h2);
+    layer<false, true, EPI_HIDDEN>(g, s);
+    const size_t Hp = (H + 31u) & ~31u, lds = 2u * (16u * (Hp + 8u) + 16u * Hp);
+    hipLaunchKernelGGL(mlp_out, dim3((N + 15u) / 16u), dim3(256), lds, s, g.O, W3, net->params + l.b3, y, N, H, dout);
+    return launch_status();
+}
+
+// Back-propagation through both hidden layers, then the three weight gradients in one launch (and
+// their parts added up in another).
+int backward_impl(const cae_mlp *net, const float *dy, float *grads, uint32_t N, void *ws, hipStream_t s)
+{
+    const uint32_t din = net->d_in, H = net->d_hidden, dout = net->d_out;
+    const Layout l = layout(din, H, dout);
+    const WsLayout w = ws_layout(din, H, dout, N);
+    unsigned char *b = static_cast<unsigned char *>(ws);
+    const uint16_t *W2 = net->weights + (size_t)din * H, *W3 = W2 + (size_t)H * H;
+    // dz2 = (dy W3^T) * silu'(z2)
+    LayerArgs g{};
+    g.Af = dy;
+    g.Acopy = reinterpret_cast<uint16_t *>(b + w.dyb);
+    g.ldc = 16u;
+    g.B = W3;
+    g.M = N;
+    g.N = H;
+    g.K = dout;
+    g.Z = reinterpret_cast<float *>(b + w.z2);
+    g.O = reinterpret_cast<uint16_t *>(b + w.dz2);
+    layer<true, false, EPI_DSILU>(g, s);
+    // dz1 = (dz2 W2^T) * silu'(z1)
+    g.A = g.O;
+    g.B = W2;
+    g.K = H;
+    g.Z = reinterpret_cast<float *>(b + w.z1);
+    g.O = reinterpret_cast<uint16_t *>(b + w.dz1);
+    layer<false, false, EPI_DSILU>(g, s);
+
+    const GradSplit sp = grad_split(H, N);
+    GradArgs a;
+    a.x = reinterpret_cast<const uint16_t *>(b + w.xb);
+    a.h1 = reinterpret_cast<const uint16_t *>(b + w.h1);
+    a.h2 = reinterpret_cast<const uint16_t *>(b + w.h2);
+    a.dy = reinterpret_cast<const uint16_t *>(b + w.dyb);
+    a.dz2 = reinterpret_cast<const uint16_t *>(b + w.dz2);
+    a.dz1 = reinterpret_cast<const uint16_t *>(b + w.dz1);
+    a.batch = N;
+    a.din = din;
+    a.H = H;
+    a.dout = dout;
+    a.parts = sp.parts;
+    a.chunk = sp.chunk;
+    a.tiles1 = sp.tiles1;
+    a.tiles2 = sp.tiles2;
+    a.tiles3 = sp.tiles3;
+    a.stride = part_stride(l.P);
+    float *out = sp.parts > 1u ? reinterpret_cast<float *>(b + w.part) : grads;  // in the parameter layout
+    a.o1 = out + l.w1;
+    a.o2 = out + l.w2;
+    a.o3 = out + l.w3;
+    const uint32_t tiles = sp.tiles1 + sp.tiles2 + sp.tiles3;
+    hipLaunchKernelGGL(mlp_grad, dim3(tiles * sp.parts), dim3(256), 0, s, a);
+    if (sp.parts > 1u)
+        hipLaunchKernelGGL(grad_reduce, dim3((uint32_t)((l.P + 1023u) / 1024u)), dim3(256), 0, s, out, sp.parts,
+                           a.stride, l.P, grads);
     return launch_status();
 }
 
 }  // namespace
-
