@@ -133,7 +133,9 @@ typedef struct cae_buffers {
 } cae_buffers;
 
 /* Schedule of the persistent launch.  Zero fields mean "choose automatically"; an
- * autotuner result can be passed back in.  waves_per_market[c] applies to size class c
+ * autotuner result can be passed back in.  A size class with waves_per_market, pipelined and pack
+ * all 0 is left to the library, which then also chooses its overlap (unless given) and packing
+ * (if every class is left to it); where waves_per_market is given, overlap and pack 0 mean off.  waves_per_market[c] applies to size class c
  * (class = index of the smallest of 64,128,256,512,1024 that is >= L, times 8, plus the
  * A bucket floor(log2(A)) clamped to 6..13 minus 6): 40 classes. */
 #define CAE_NUM_CLASSES 40

@@ -2314,13 +2314,89 @@ EngineFn engine_fn(uint32_t tpl_max, bool mid, bool trace, bool pack)
     return trace ? engine_fn_t<false, true>(tpl_max, pack) : engine_fn_t<false, false>(tpl_max, pack);
 }
 
-uint32_t auto_wpm(uint32_t L, uint32_t A)
+// The waves per market that bounds what a caller's waves_per_group may be when it leaves the
+// class's waves to the library.
+uint32_t auto_wpm(uint32_t A)
 {
-    (void)L;
     // about 8 agents per lane per step, at most 16 waves
     uint32_t w = 1;
     while (w < 16 && 64u * 8u * (2u * w) <= A) w <<= 1;
     return w;
+}
+
+struct AutoClass {
+    uint32_t wpm, overlap;
+};
+
+// Schedule of a size class whose waves the caller leaves to the library: tpl ticks per lane, A
+// agents (the class's mean), `full` waves that would spread the chip's 16 waves per CU over the
+// ensemble in proportion to cost (4096 / M for M equal markets on 256 CUs), plain: some market of
+// the class does not run the last-tick Philox model.
+//   * A market gets its share of the waves, as long as every wave has work: a row of 64 agents
+//     each when the chip is nearly empty (full >= 16), two rows otherwise; few agents or a book
+//     longer than the order flow fill one wave (the clearing is one wave's work whatever the
+//     group).  L = 256, A = 1024, us per step for one wave / this rule: M = 64 1.9 / 0.82 (16
+//     waves), M = 512 1.8 / 1.10 (8), M = 1024 2.9 / 1.74 (4), M = 4096 6.8 / 6.8 (1).
+//   * The next step's orders are generated during the clearing (overlap) where that clearing is
+//     short against them: always for books of up to 4 ticks per lane (M = 1024: 2.08 -> 1.74),
+//     for longer ones only with enough agents (L = 512, A = 512, M = 64: 1.54 with, 1.18 without).
+//     The clearing wave's share of the rows is what its clearing leaves of an even one.
+// Over 300 shapes (L 64..1024, A 16..16384, M 4..8192) the rule is within 1.1 % of the best of the
+// schedules it chooses from, in geometric mean (17 % at most); a rule on A alone lost 15 %.
+AutoClass auto_class(uint32_t tpl, double A, double full, bool plain)
+{
+    const uint32_t rows = (uint32_t)std::ceil(A / 64.0);
+    AutoClass c{1u, 0u};
+    if (A <= 128.0) return c;
+    double cap;
+    if (full >= 16.0) {
+        cap = rows <= 4u || (!plain && (tpl <= 4u || A >= 2048.0)) ? rows : rows / 2.0;
+    } else {
+        cap = plain ? rows / 4.0 : rows / 2.0;
+        if (tpl >= 8u) cap = std::min(cap, A / (32.0 * tpl));
+    }
+    const double w = std::min({full, cap, 16.0});
+    while (2.0 * c.wpm <= w) c.wpm <<= 1;
+    if (c.wpm < 2u || plain || (tpl >= 8u && full >= 16.0 && A < 2048.0)) return c;
+    const uint32_t even = rows / c.wpm;
+    uint32_t share = 0;
+    if (tpl >= 16u || (tpl == 8u && (A < 2048.0 || full >= 8.0))) share = 0;
+    else if (even >= 8u) share = 3u * even / 4u;
+    else if (even >= 3u) share = c.wpm == 4u ? even - 1u : even / 2u;
+    c.overlap = share + 1u;
+    return c;
+}
+
+// The same for a class of a mixed ensemble, whose costliest class costs more than 1.5 times the
+// mean: every market runs the same steps, so the costliest hold the launch, and the workgroups
+// left over balance it only if there are more of them than fit at once.  `full` as above, for
+// this class and for the costliest (full_max): groups of up to full_max waves, and four times the
+// share of the waves per market (twice when there are several markets per wave slot anyway).
+// Uneven ensembles (L 64..1024, A 64..16384), us per step of the rule above / this one: M = 256
+// 5.1 / 4.9, M = 1024 10.2 / 6.7, M = 4096 27 / 19; half A = 64, half A = 4096: M = 4096 17 / 12.
+AutoClass auto_class_mixed(double A, double full, double full_max, bool plain)
+{
+    const uint32_t rows = (uint32_t)std::ceil(A / 64.0);
+    AutoClass c{1u, 0u};
+    if (A <= 128.0) return c;
+    uint32_t cap = 4u;
+    while (cap < 16u && 2.0 * cap <= 1.1 * full_max) cap <<= 1;
+    const double w = std::min({(full_max < 2.5 ? 2.0 : 4.0) * full, (double)cap, plain ? rows / 2.0 : (double)rows});
+    while (2.0 * c.wpm <= w) c.wpm <<= 1;
+    if (c.wpm >= 2u && !plain) c.overlap = (uint32_t)std::max(1.0, 0.75 * A / 64.0 / c.wpm);
+    return c;
+}
+
+// Markets per wave (2 or 4, 0: off) of an ensemble of small last-tick Philox markets left to the
+// library: packing pays once one wave per market would give a SIMD several waves that are mostly
+// idle lanes.  L = 128, us per step unpacked / packed: A = 16, M = 2048 0.89 / 0.82, M = 8192
+// 2.41 / 1.25; A = 64, M = 4096 1.36 / 1.33 (two), M = 8192 2.53 / 1.97; A = 128, M = 4096 1.62 /
+// 1.76 (not packed), M = 8192 3.29 / 2.86.
+uint32_t auto_pack(uint32_t A_max, double waves_per_cu)
+{
+    if ((A_max <= 32u && waves_per_cu >= 8.0) || (A_max <= 128u && waves_per_cu >= 32.0)) return 4u;
+    if (A_max <= 64u && waves_per_cu >= 16.0) return 2u;
+    return 0u;
 }
 
 }  // namespace
@@ -2359,11 +2435,62 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
         e->any_mid |= (e->desc[m].flags & CAE_MODEL_MASK) == CAE_MODEL_MID ||
                       ((e->desc[m].flags >> CAE_GEN_SHIFT) & 0xFFu) == CAE_GEN_SPLITMIX;
     std::vector<uint32_t> packp(M, 0u);
+    uint32_t ncu = 0;
+    int rc = device_cus(e->device, &ncu);
+    if (rc) return rc;
     for (uint32_t c = 0; c < CAE_NUM_CLASSES; ++c)
         if (t.pack[c] != 0 && t.pack[c] != 2 && t.pack[c] != 4) return fail(CAE_EINVAL, "pack[%u] must be 0, 2 or 4", c);
     uint32_t maxL = 0;
     for (uint32_t m = 0; m < M; ++m) maxL = std::max(maxL, e->desc[m].L);
     e->any_pack = false;
+    // the classes left to the library (no waves, mode or packing given): one schedule per class,
+    // from its share of the ensemble's cost
+    bool auto_c[CAE_NUM_CLASSES] = {}, auto_ov[CAE_NUM_CLASSES] = {};
+    {
+        double cost[CAE_NUM_CLASSES] = {}, agents[CAE_NUM_CLASSES] = {}, total = 0.0, dearest = 0.0;
+        uint32_t count[CAE_NUM_CLASSES] = {}, need[CAE_NUM_CLASSES] = {}, A_max = 0;
+        bool plain[CAE_NUM_CLASSES] = {}, all_auto = true, any_plain = false;
+        for (uint32_t m = 0; m < M; ++m) {
+            const cae_market &d = e->desc[m];
+            const uint32_t c = lclass(d.L) * 8u + aclass(d.A);
+            const double w = (double)d.A + 2.0 * 64.0 * tpl_for(d.L);
+            count[c] += 1;
+            cost[c] += w;
+            agents[c] += d.A;
+            total += w;
+            plain[c] |= (d.flags & 0xFFFFu) != 0u;
+            need[c] = std::max(need[c], auto_wpm(d.A));
+            A_max = std::max(A_max, d.A);
+        }
+        for (uint32_t c = 0; c < CAE_NUM_CLASSES; ++c) {
+            if (!count[c]) continue;
+            auto_c[c] = t.waves_per_market[c] == 0 && t.pipelined[c] == 0 && t.pack[c] == 0;
+            all_auto = all_auto && auto_c[c] && t.overlap[c] == 0;
+            any_plain |= plain[c];
+            dearest = std::max(dearest, cost[c] / count[c]);
+        }
+        const uint32_t P = all_auto && !any_plain && maxL <= kPackMaxL ? auto_pack(A_max, (double)M / ncu) : 0u;
+        for (uint32_t c = 0; c < CAE_NUM_CLASSES; ++c) {
+            if (!count[c] || !auto_c[c]) continue;
+            if (P) {
+                t.pack[c] = (uint8_t)P;
+                continue;
+            }
+            const double full = 16.0 * ncu * (cost[c] / count[c]) / total;
+            const double A = agents[c] / count[c];
+            AutoClass a = dearest > 1.5 * total / M
+                              ? auto_class_mixed(A, full, 16.0 * ncu * dearest / total, plain[c])
+                              : auto_class(1u << (c / 8u), A, full, plain[c]);
+            // a caller's group size below what the class's markets need is refused further down
+            if (t.waves_per_group && need[c] > t.waves_per_group) a.wpm = need[c];
+            while (t.waves_per_group && need[c] <= t.waves_per_group && a.wpm > t.waves_per_group) a.wpm >>= 1;
+            t.waves_per_market[c] = (uint8_t)a.wpm;
+            if (t.overlap[c] == 0 && a.wpm >= 2u) {
+                t.overlap[c] = (uint8_t)std::min(a.overlap, 255u);
+                auto_ov[c] = true;
+            }
+        }
+    }
     for (uint32_t m = 0; m < M; ++m) {
         const cae_market &d = e->desc[m];
         const uint32_t c = lclass(d.L) * 8u + aclass(d.A);
@@ -2377,7 +2504,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             continue;
         }
         uint32_t w = t.waves_per_market[c];
-        if (w == 0) w = auto_wpm(d.L, d.A);
+        if (w == 0) w = auto_wpm(d.A);  // a packed class's market that cannot be packed
         if (w > 16 || (w & (w - 1)) != 0) return fail(CAE_EINVAL, "waves_per_market[%u]=%u not a power of 2 <= 16", c, w);
         if (t.pipelined[c] > 1) return fail(CAE_EINVAL, "pipelined[%u] must be 0 or 1", c);
         if (t.pipelined[c]) w = 1;  // a pipelined pair uses the whole workgroup
@@ -2430,7 +2557,9 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
         const uint32_t c = lclass(e->desc[m].L) * 8u + aclass(e->desc[m].A);
         // overlapped markets keep two buffers of bins in LDS; wider offset ranges run plain
         const bool mid = (e->desc[m].flags & CAE_MODEL_MASK) == CAE_MODEL_MID;
-        const uint32_t ov = e->desc[m].K <= (mid ? kMaxOverlapKMid : kMaxOverlapK) ? t.overlap[c] : 0u;
+        uint32_t ov = e->desc[m].K <= (mid ? kMaxOverlapKMid : kMaxOverlapK) ? t.overlap[c] : 0u;
+        // (the bins of a wide offset range may not fit a caller's LDS budget)
+        if (ov && auto_ov[c] && 4u * (2u * 64u * tp + 2u * hwords_for(e->desc[m].K, mid) + kScr) > lds_budget) ov = 0u;
         uint32_t pp = t.pipelined[c] ? 1u : (ov ? 2u : 0u);
         uint32_t share = ov ? ov - 1u : 0u;
         uint32_t hw = ov ? hwords_for(e->desc[m].K, mid) : 0u;
@@ -2531,9 +2660,6 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     e->waves_per_group = G;
     e->lds_bytes = lds_max;
 
-    uint32_t ncu = 0;
-    int rc = device_cus(e->device, &ncu);
-    if (rc) return rc;
     int per_cu = 0;
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(engine_fn(tpl_max, e->any_mid, false, e->any_pack)),
                                                          (int)(G * 64u), (size_t)lds_max));
