@@ -7,8 +7,7 @@
 //
 // Precision: weights, inputs, hidden activations and back-propagated gradients are stored in
 // bfloat16 (round to nearest even); every product is accumulated in fp32 on the matrix cores
-// (gfx950's v_mfma_f32_32x32x16_bf16 and v_mfma_f32_16x16x32_bf16; the fused inference kernel
-// v_mfma_f32_16x16x16bf16_1k, whose chains give the same bits); biases, pre-activations, outputs, weight
+// (gfx950's v_mfma_f32_32x32x16_bf16 and v_mfma_f32_16x16x32_bf16); biases, pre-activations, outputs, weight
 // gradients and the Adam state are fp32.  Parameter layout (row-major, input index first):
 //   W1[d_in][H], b1[H], W2[H][H], b2[H], W3[H][d_out], b3[d_out]
 // and the bfloat16 weight copies are W1, W2, W3 in the same layouts, back to back, followed by
@@ -70,9 +69,24 @@ __device__ __forceinline__ uint4 ld8u(const uint16_t *base, uint32_t bytes)
     return ld8u(reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + bytes));
 }
 
+__device__ __forceinline__ uint16_t ld1u(const uint16_t *base, uint32_t bytes)
+{
+    return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + bytes);
+}
+
 __device__ __forceinline__ v8bf ld8(const uint16_t *p)  // eight bfloat16, 16-byte aligned
 {
     return __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(p));
+}
+
+__device__ __forceinline__ v8bf pack8(const uint16_t (&e)[8])
+{
+    uint4 u;
+    u.x = (uint32_t)e[0] | ((uint32_t)e[1] << 16);
+    u.y = (uint32_t)e[2] | ((uint32_t)e[3] << 16);
+    u.z = (uint32_t)e[4] | ((uint32_t)e[5] << 16);
+    u.w = (uint32_t)e[6] | ((uint32_t)e[7] << 16);
+    return __builtin_bit_cast(v8bf, u);
 }
 
 // Four bfloat16 of a k-major LDS tile, transposed: within each 16 lanes, lane i addresses row
@@ -796,132 +810,229 @@ __global__ void __launch_bounds__(256) adam_step(const AdamArgs a)
     else if (i >= a.l.w3 && i < a.l.b3) a.wb[a.l.b1 + (a.l.b2 - a.l.w2) + (i - a.l.w3)] = f2bf(pi);
 }
 
-// Inference of the whole network for kPredRows rows per workgroup (four waves), in one launch.
-// The input tile and both hidden activations stay in LDS (bf16, rows padded by 8 elements);
-// the layer products use the same MFMA tiles, k order and rounding points as mlp_layer, so the
-// outputs equal cae_mlp_forward's bit for bit.
-constexpr uint32_t kPredRows = 32;
-constexpr uint32_t kPredPad = 8;
-constexpr uint32_t kPredMaxH = 496;  // keeps the workgroup's LDS within 64 KiB
+// Inference of the whole network in one launch: a workgroup of 16 waves keeps its weights over
+// all of its tiles of rows.  A wave owns NT 16-column tiles of each hidden layer, over RT blocks
+// of 16 rows; narrow layers (H <= 128) split the waves over 2 or 4 groups of rows.  With RES
+// (H <= 256) the wave's W2 fragments stay in registers, otherwise they come from L2 for every
+// tile, whose RT = 4 blocks of rows share them.  The input of the next tile is fetched under the
+// current one, both hidden activations go through LDS, W3 sits in LDS as rows of 16 columns read
+// transposed; the output layer of 16 rows is one wave's chain, under the others' next tile.
+// Same rounding points and the same chains over k as mlp_layer and mlp_out, so the outputs equal
+// cae_mlp_forward's bit for bit.
+// H = 256: 6553 rows take 12.1 us, 65536 rows 39.6, one row 9.3 (32-row tiles on four waves that
+// streamed W2 from L2 for each: 21.5, 82.3 and 20.1); H = 496, 65536 rows: 134 (231).  A tile of 32
+// rows costs 2 us, of which the exponentials' instructions are 1.6; the set-up is instructions and
+// two memory latencies, about 7 us.
+constexpr uint32_t kPredMaxH = 496;
+constexpr uint32_t kPredWaves = 16, kPredThreads = 64 * kPredWaves;
 
 struct PredArgs {
     const float *x;
     float *y;
     uint32_t N, din, H, dout;
+    uint32_t cols_log2;  // log2 of the waves along the columns
     const uint16_t *W1, *W2T, *W3;
     const float *b1, *b2, *b3;
 };
 
-__device__ __forceinline__ v4s lds_frag(const uint16_t *p)  // four consecutive bf16
-{
-    const uint2 v = *reinterpret_cast<const uint2 *>(p);
-    v4s r;
-    r[0] = (short)(v.x & 0xFFFFu);
-    r[1] = (short)(v.x >> 16);
-    r[2] = (short)(v.y & 0xFFFFu);
-    r[3] = (short)(v.y >> 16);
-    return r;
-}
-
-__global__ void __launch_bounds__(256) mlp_predict(const PredArgs a)
+template <uint32_t NT, bool RES, uint32_t RT>
+__global__ void __launch_bounds__(kPredThreads) mlp_predict(const PredArgs a)
 {
     extern __shared__ __align__(16) uint16_t plds[];
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t r16 = lane & 15u, grp = lane >> 4;
-    const uint32_t row0 = blockIdx.x * kPredRows;
-    const uint32_t Kx = (a.din + 15u) & ~15u;  // input width padded to the MFMA depth
-    const uint32_t ldh = a.H + kPredPad;
-    uint16_t *xs = plds;                        // [kPredRows][Kx]
-    uint16_t *h1 = xs + kPredRows * Kx;          // [kPredRows][ldh]
-    uint16_t *h2 = h1 + kPredRows * ldh;         // [kPredRows][ldh]
-    for (uint32_t i = threadIdx.x; i < kPredRows * Kx; i += 256u) {
-        const uint32_t r = i / Kx, c = i % Kx;
-        xs[i] = (row0 + r < a.N && c < a.din) ? f2bf(a.x[(size_t)(row0 + r) * a.din + c]) : (uint16_t)0;
-    }
-    __syncthreads();
-    const uint32_t ct = a.H / 16u;  // column tiles of a hidden layer
-    // layer 1: h1 = silu(x W1 + b1)
-    for (uint32_t j = wave; j < ct; j += 4u) {
-        const uint32_t n = 16u * j + r16;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t r = lane & 15u, g = lane >> 4;
+    const uint32_t H = a.H, Hp = (H + 31u) & ~31u, ldh = Hp + 8u, ct = H / 16u;
+    const uint32_t Kx = (a.din + 31u) & ~31u, ldx = Kx + 8u;
+    const uint32_t wcols = 1u << a.cols_log2, wc = wave & (wcols - 1u), rg = wave >> a.cols_log2;
+    const uint32_t groups = kPredWaves >> a.cols_log2, rows = 16u * RT * groups;  // rows of a tile
+    // [rows][ldh] twice, the input [rows][ldx] twice, [Hp][16]
+    uint16_t *h1 = plds, *h2 = h1 + rows * ldh, *xs = h2 + rows * ldh, *w3s = xs + 2u * rows * ldx;
+    constexpr uint32_t K2 = 8;  // steps of 32 over H <= 256
+    const uint32_t tiles = (a.N + rows - 1u) / rows;
+
+    // Every wave of the CU issues the set-up once (about 7 ns per instruction), so it is kept short:
+    // 32-bit offsets from uniform bases, no division per element.
+    // The input tile is contiguous: at most XN values per thread, thread tid + 1024 i.
+    constexpr uint32_t XN = 4u;
+    const uint32_t xcount = rows * a.din;
+    float xv[XN];
+    uint32_t xo[XN];  // where they go in the LDS tile
+    auto load_x = [&](uint32_t tile) {
+        const uint64_t first = (uint64_t)tile * xcount;
+        const float *base = a.x + first;
+        const uint64_t left = (uint64_t)a.N * a.din - first;  // >= 1
+        const uint32_t last = left > xcount ? xcount - 1u : (uint32_t)left - 1u;
 #pragma unroll
-        for (uint32_t rt = 0; rt < kPredRows / 16u; ++rt) {
-            v4f acc = {0.f, 0.f, 0.f, 0.f};
-            for (uint32_t k0 = 0; k0 < Kx; k0 += 16u) {
-                const v4s av = lds_frag(xs + (16u * rt + r16) * Kx + k0 + 4u * grp);
-                v4s bv;
+        for (uint32_t i = 0; i < XN; ++i)
+            if (kPredThreads * i < xcount) xv[i] = base[min(tid + kPredThreads * i, last)];
+    };
+    auto store_x = [&](uint16_t *to) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const uint32_t k = k0 + 4u * grp + (uint32_t)t;
-                    bv[t] = (short)(k < a.din ? a.W1[(size_t)k * a.H + n] : (uint16_t)0);
-                }
-                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
-            }
+        for (uint32_t i = 0; i < XN; ++i)
+            if (kPredThreads * i < xcount && tid + kPredThreads * i < xcount) to[xo[i]] = f2bf(xv[i]);
+    };
+    load_x(blockIdx.x);
+    // the wave's weights (W1's rows past the input and W2T's past a ragged H are masked; W1 is
+    // followed by W2 and W2T, so up to 64 of its rows may be read)
+    v8bf w2[NT][RES ? K2 : 1];
+    float b1[NT], b2[NT];
+    const uint32_t klim = H == Hp ? 0xFFFFFFFFu : H - 8u;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float z = acc[t] + a.b1[n];
-                h1[(16u * rt + 4u * grp + (uint32_t)t) * ldh + n] = f2bf(silu(z));
-            }
+    for (uint32_t j = 0; j < NT; ++j) {
+        const uint32_t n = min(16u * (wc + wcols * j), H - 16u) + r;  // a missing tile repeats the last
+        b1[j] = a.b1[n];
+        b2[j] = a.b2[n];
+        if constexpr (RES) {
+#pragma unroll
+            for (uint32_t u = 0; u < K2; ++u)
+                if (32u * u < H) w2[j][u] = __builtin_bit_cast(v8bf, ld8u(a.W2T, 2u * (n * H + min(32u * u + 8u * g, klim))));
         }
     }
+    auto load_w1 = [&](uint32_t j, uint32_t k0) {
+        const uint32_t n = min(16u * (wc + wcols * j), H - 16u) + r, k = k0 + 8u * g;
+        const uint32_t off = 2u * (k * H + n);
+        uint16_t e[8];
+#pragma unroll
+        for (uint32_t t = 0; t < 8u; ++t) e[t] = ld1u(a.W1 + (size_t)t * H, off);
+#pragma unroll
+        for (uint32_t t = 0; t < 8u; ++t) e[t] = k + t < a.din ? e[t] : (uint16_t)0;
+        return pack8(e);
+    };
+    v8bf w1[NT];
+#pragma unroll
+    for (uint32_t j = 0; j < NT; ++j) w1[j] = load_w1(j, 0u);
+    const float b3 = a.b3[min(r, a.dout - 1u)];
+    {
+        const uint32_t k = tid >> 4, c = tid & 15u, off = 2u * (k * a.dout + min(c, a.dout - 1u));
+        for (uint32_t k0 = 0; k0 < Hp; k0 += 64u) {  // 64 rows of W3 per turn
+            const uint16_t w = ld1u(a.W3 + (size_t)min(k0, H - 16u) * a.dout, k0 + k < H ? off : 0u);
+            if (k0 + k < Hp) w3s[(k0 + k) * 16u + c] = (k0 + k < H && c < a.dout) ? w : (uint16_t)0;
+        }
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < XN; ++i)
+        if (kPredThreads * i < xcount) {
+            const uint32_t e = tid + kPredThreads * i, row = e / a.din;
+            xo[i] = row * ldx + (e - row * a.din);
+        }
+    if (RES && H != Hp) {  // the last step's second half lies past H
+#pragma unroll
+        for (uint32_t j = 0; j < NT; ++j)
+#pragma unroll
+            for (uint32_t u = 0; u < (RES ? K2 : 1u); ++u)
+                w2[j][u] = __builtin_bit_cast(v8bf, keep(32u * u + 8u * g < H, __builtin_bit_cast(uint4, w2[j][u])));
+    }
+    // zero columns past the widths (rows of the input tiles are a multiple of 16 bytes)
+    for (uint32_t e = tid; e < rows * ldx / 4u; e += kPredThreads) reinterpret_cast<uint4 *>(xs)[e] = make_uint4(0, 0, 0, 0);
+    if (H != Hp) {
+        for (uint32_t e = tid; e < 2u * rows * 16u; e += kPredThreads) h1[(e >> 4) * ldh + H + (e & 15u)] = 0;
+    }
     __syncthreads();
-    // layer 2: h2 = silu(h1 W2 + b2), B fragments from W2T (8 bytes per lane)
-    for (uint32_t j = wave; j < ct; j += 4u) {
-        const uint32_t n = 16u * j + r16;
-        v4f acc[kPredRows / 16u];
+    store_x(xs);
+    load_x(min(blockIdx.x + gridDim.x, tiles - 1u));
+    __syncthreads();
+    uint32_t turn = 0, buf = 0;
+    for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const uint32_t row0 = rg * 16u * RT;  // the wave's rows of the tile
+        uint16_t *xb = xs + buf * rows * ldx, *xn = xs + (buf ^ 1u) * rows * ldx;
+        v4f acc[RT][NT];
+        // layer 1
 #pragma unroll
-        for (uint32_t rt = 0; rt < kPredRows / 16u; ++rt) acc[rt] = v4f{0.f, 0.f, 0.f, 0.f};
-        const uint16_t *wrow = a.W2T + (size_t)n * a.H + 4u * grp;
-        for (uint32_t k0 = 0; k0 < a.H; k0 += 128u) {
-            v4s bv[8];
+        for (uint32_t q = 0; q < RT; ++q) {
+            const v8bf f = frag<16, false>(xb, ldx, row0 + 16u * q, 0u, lane);
 #pragma unroll
-            for (uint32_t u = 0; u < 8u; ++u)
-                if (k0 + 16u * u < a.H) {
-                    const uint2 v = *reinterpret_cast<const uint2 *>(wrow + k0 + 16u * u);
-                    bv[u][0] = (short)(v.x & 0xFFFFu);
-                    bv[u][1] = (short)(v.x >> 16);
-                    bv[u][2] = (short)(v.y & 0xFFFFu);
-                    bv[u][3] = (short)(v.y >> 16);
+            for (uint32_t j = 0; j < NT; ++j) acc[q][j] = Mfma<16>::mac(f, w1[j], v4f{0.f, 0.f, 0.f, 0.f});
+        }
+        if (Kx > 32u) {
+#pragma unroll
+            for (uint32_t j = 0; j < NT; ++j) {
+                const v8bf w = load_w1(j, 32u);
+#pragma unroll
+                for (uint32_t q = 0; q < RT; ++q)
+                    acc[q][j] = Mfma<16>::mac(frag<16, false>(xb, ldx, row0 + 16u * q, 32u, lane), w, acc[q][j]);
+            }
+        }
+        auto activate = [&](uint16_t *h, const float (&b)[NT]) {
+#pragma unroll
+            for (uint32_t j = 0; j < NT; ++j) {
+                const uint32_t c = wc + wcols * j;
+                if (c < ct) {
+#pragma unroll
+                    for (uint32_t q = 0; q < RT; ++q)
+#pragma unroll
+                        for (uint32_t t = 0; t < 4u; ++t)
+                            h[(row0 + 16u * q + 4u * g + t) * ldh + 16u * c + r] = f2bf_hw(silu(acc[q][j][t] + b[j]));
                 }
+            }
+        };
+        activate(h1, b1);
+        store_x(xn);
+        load_x(min(tile + 2u * gridDim.x, tiles - 1u));
+        __syncthreads();
+        // layer 2
 #pragma unroll
-            for (uint32_t u = 0; u < 8u; ++u)
-                if (k0 + 16u * u < a.H) {
+        for (uint32_t q = 0; q < RT; ++q)
 #pragma unroll
-                    for (uint32_t rt = 0; rt < kPredRows / 16u; ++rt) {
-                        const v4s av = lds_frag(h1 + (16u * rt + r16) * ldh + k0 + 16u * u + 4u * grp);
-                        acc[rt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv[u], acc[rt], 0, 0, 0);
+            for (uint32_t j = 0; j < NT; ++j) acc[q][j] = v4f{0.f, 0.f, 0.f, 0.f};
+        if constexpr (RES) {
+#pragma unroll
+            for (uint32_t u = 0; u < K2; ++u)
+                if (32u * u < H) {
+#pragma unroll
+                    for (uint32_t q = 0; q < RT; ++q) {
+                        const v8bf f = frag<16, false>(h1, ldh, row0 + 16u * q, 32u * u, lane);
+#pragma unroll
+                        for (uint32_t j = 0; j < NT; ++j) acc[q][j] = Mfma<16>::mac(f, w2[j][u], acc[q][j]);
                     }
                 }
-        }
+        } else {
+            constexpr uint32_t KB = 2;  // steps whose weights are in flight together
+#pragma unroll 1
+            for (uint32_t k0 = 0; k0 < H; k0 += 32u * KB) {
+                uint4 w[KB][NT];
 #pragma unroll
-        for (uint32_t rt = 0; rt < kPredRows / 16u; ++rt)
+                for (uint32_t u = 0; u < KB; ++u)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float z = acc[rt][t] + a.b2[n];
-                h2[(16u * rt + 4u * grp + (uint32_t)t) * ldh + n] = f2bf(silu(z));
-            }
-    }
-    __syncthreads();
-    // layer 3: y = h2 W3 + b3 (one column tile, one row tile per wave)
-    if (wave < kPredRows / 16u) {
-        const uint32_t rt = wave, n = r16;
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-        for (uint32_t k0 = 0; k0 < a.H; k0 += 16u) {
-            const v4s av = lds_frag(h2 + (16u * rt + r16) * ldh + k0 + 4u * grp);
-            v4s bv;
+                    for (uint32_t j = 0; j < NT; ++j) {
+                        const uint32_t n = min(16u * (wc + wcols * j), H - 16u) + r, k = k0 + 32u * u + 8u * g;
+                        w[u][j] = ld8u(a.W2T + (size_t)n * H + min(k, H - 8u));
+                    }
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint32_t k = k0 + 4u * grp + (uint32_t)t;
-                bv[t] = (short)(n < a.dout ? a.W3[(size_t)k * a.dout + n] : (uint16_t)0);
-            }
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
-        }
-        if (n < a.dout) {
+                for (uint32_t u = 0; u < KB; ++u)
+                    if (k0 + 32u * u < H) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint32_t r = row0 + 16u * rt + 4u * grp + (uint32_t)t;
-                if (r < a.N) a.y[(size_t)r * a.dout + n] = acc[t] + a.b3[n];
+                        for (uint32_t j = 0; j < NT; ++j) w[u][j] = keep(k0 + 32u * u + 8u * g < H, w[u][j]);
+#pragma unroll
+                        for (uint32_t q = 0; q < RT; ++q) {
+                            const v8bf f = frag<16, false>(h1, ldh, row0 + 16u * q, k0 + 32u * u, lane);
+#pragma unroll
+                            for (uint32_t j = 0; j < NT; ++j)
+                                acc[q][j] = Mfma<16>::mac(f, __builtin_bit_cast(v8bf, w[u][j]), acc[q][j]);
+                        }
+                    }
             }
         }
+        activate(h2, b2);
+        __syncthreads();
+        // layer 3, 16 rows to a wave; it passes the next tile's first barrier before h2 is
+        // written again
+        const uint32_t blocks = RT * groups, q = (wave + kPredWaves - turn) % kPredWaves;
+        if (q < blocks) {
+            v4f y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (uint32_t k0 = 0; k0 < Hp; k0 += 32u)
+                y = Mfma<16>::mac(frag<16, false>(h2, ldh, 16u * q, k0, lane), frag<16, true>(w3s, 16u, 0u, k0, lane), y);
+            if (r < a.dout) {
+#pragma unroll
+                for (uint32_t t = 0; t < 4u; ++t) {
+                    const uint64_t row = (uint64_t)tile * rows + 16u * q + 4u * g + t;
+                    if (row < a.N) a.y[row * a.dout + r] = y[t] + b3;
+                }
+            }
+        }
+        turn = (turn + blocks) % kPredWaves;
+        buf ^= 1u;
     }
 }
 
@@ -951,16 +1062,6 @@ constexpr uint32_t kLoadAhead = 8;
 constexpr uint32_t kTrainMaxH = 256;
 constexpr uint32_t kTrainMaxIn = 32;
 constexpr uint32_t kTrainPad = 8;  // bf16 elements of padding per LDS row
-
-__device__ __forceinline__ v8bf pack8(const uint16_t (&e)[8])
-{
-    uint4 u;
-    u.x = (uint32_t)e[0] | ((uint32_t)e[1] << 16);
-    u.y = (uint32_t)e[2] | ((uint32_t)e[3] << 16);
-    u.z = (uint32_t)e[4] | ((uint32_t)e[5] << 16);
-    u.w = (uint32_t)e[6] | ((uint32_t)e[7] << 16);
-    return __builtin_bit_cast(v8bf, u);
-}
 
 __device__ __forceinline__ v4f mfma32(v8bf a, v8bf b, v4f c)
 {
@@ -1555,9 +1656,31 @@ int cae_mlp_predict(const cae_mlp *net, const float *x, float *y, uint32_t N, vo
     a.b1 = net->params + l.b1;
     a.b2 = net->params + l.b2;
     a.b3 = net->params + l.b3;
-    const size_t lds = 2ull * (kPredRows * ((din + 15u) & ~15u) + 2ull * kPredRows * (H + kPredPad));
-    const uint32_t blocks = (N + kPredRows - 1u) / kPredRows;
-    hipLaunchKernelGGL(mlp_predict, dim3(blocks), dim3(256), lds, (hipStream_t)stream, a);
+    int dev = 0, cus = 0;
+    hipError_t he = hipGetDevice(&dev);
+    if (he == hipSuccess) he = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (he != hipSuccess) return mfail(CAE_EHIP, hipGetErrorString(he));
+    a.cols_log2 = H > 128u ? 4u : (H > 64u ? 3u : 2u);
+    const uint32_t groups = kPredWaves >> a.cols_log2;
+    const uint64_t Hp = (H + 31u) & ~31u, Kx = (din + 31u) & ~31u;
+    // blocks of 16 rows per wave: more rows share each pass over the weights, once every CU has a
+    // tile of them; the tile's input is at most four values per thread
+    const auto lds_bytes = [&](uint64_t rows) { return 2u * (2u * rows * (Hp + 8u) + 2u * rows * (Kx + 8u) + Hp * 16u); };
+    uint32_t rt = 1;
+    const uint32_t most = H > 256u ? 4u : 2u;
+    while (2u * rt <= most && (uint64_t)16u * rt * groups * (uint32_t)cus < N &&
+           32u * rt * groups * din <= 4u * kPredThreads && lds_bytes(32u * rt * groups) <= 160u * 1024u)
+        rt *= 2u;
+    const uint32_t rows = 16u * rt * groups;
+    const size_t lds = lds_bytes(rows);
+    const uint32_t tiles = (uint32_t)(((uint64_t)N + rows - 1u) / rows);
+    const dim3 grid(std::min(tiles, (uint32_t)cus)), block(kPredThreads);
+    const hipStream_t s = (hipStream_t)stream;
+    if (H <= 256u && rt == 1u) hipLaunchKernelGGL((mlp_predict<1, true, 1>), grid, block, lds, s, a);
+    else if (H <= 256u) hipLaunchKernelGGL((mlp_predict<1, true, 2>), grid, block, lds, s, a);
+    else if (rt == 1u) hipLaunchKernelGGL((mlp_predict<2, false, 1>), grid, block, lds, s, a);
+    else if (rt == 2u) hipLaunchKernelGGL((mlp_predict<2, false, 2>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((mlp_predict<2, false, 4>), grid, block, lds, s, a);
     return launch_status();
 }
 

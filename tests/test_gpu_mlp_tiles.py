@@ -115,3 +115,16 @@ def test_loss_gradient_in_place_and_split(n, delta):
     # r rounds once in fp32 (2^-24 of the larger operand), so dy is off by a few 1e-7 of its scale
     assert np.max(np.abs(out.cpu().numpy() - dy)) < 1e-6 * np.max(np.abs(dy))
     assert abs(float(l0.item()) - loss) < 1e-5 * loss
+
+
+# two and four groups of rows to a workgroup, one or several blocks of 16 rows to a wave, a
+# workgroup with several tiles and a short last one, inputs past 32 columns
+@pytest.mark.parametrize("dims,N", [((9, 112, 5), 20000), ((2, 64, 2), 40001), ((64, 16, 16), 5),
+                                    ((40, 304, 3), 9000), ((64, 256, 1), 8209)])
+def test_predict_tiles_equal_forward(dims, N):
+    import torch
+    M = _mlp()
+    net = M.MLP(*dims, max_batch=8192, seed=6)
+    x = torch.from_numpy(np.random.default_rng(7).normal(0, 1, (N, dims[0])).astype(np.float32)).cuda()
+    yf = torch.cat([net.forward(x[i:i + 8192].contiguous()) for i in range(0, N, 8192)])
+    assert torch.equal(net.predict(x), yf)
