@@ -265,8 +265,9 @@ int cae_get_tuning(const cae_ensemble *e, cae_tuning *out);
  * errors as cae_step. */
 int cae_step_naive(cae_ensemble *e, uint32_t S);
 
-/* Duration in milliseconds of the last cae_step or cae_step_naive launch, from HIP events
- * recorded on the ensemble's stream around the kernel; waits for that launch to finish. */
+/* Duration in milliseconds of the last cae_step or cae_step_naive launch, from its first
+ * workgroup's start to its last one's end by the device's constant-rate clock (10 ns); waits for
+ * the work on the ensemble's stream to finish. */
 int cae_last_step_ms(cae_ensemble *e, float *ms);
 
 /* Release the host handle made by cae_create (host metadata only).  The device buffers, which
