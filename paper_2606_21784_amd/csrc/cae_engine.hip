@@ -100,6 +100,31 @@ __device__ __forceinline__ void trace_step(const EngineArgs &args, uint32_t m, u
     if (args.tr_vol != nullptr) args.tr_vol[at] = v;
 }
 
+// A wave's recorded steps, one per lane (j: the step's index in the buffer), stored as a row of
+// consecutive words when the buffer ends: a step costs three instructions instead of two masked
+// stores (L = 128, A = 256, M = 960, us per step on one wave per market: 1.39 -> 1.28; overlapped on
+// two: 1.09 -> 0.94).
+struct TraceBuf {
+    uint32_t price = 0, vol = 0;
+
+    __device__ __forceinline__ void add(uint32_t j, uint32_t last, uint32_t v, uint32_t lane)
+    {
+        const bool mine = lane == j;
+        price = mine ? last : price;
+        vol = mine ? v : vol;
+    }
+
+    // steps [i0, i0 + n) of market m lie in lanes 0 .. n - 1
+    __device__ __forceinline__ void store(const EngineArgs &args, uint32_t m, uint32_t i0, uint32_t n,
+                                          uint32_t lane) const
+    {
+        if (lane >= n) return;
+        const uint64_t at = (uint64_t)m * args.tr_ld + i0 + lane;
+        if (args.tr_price != nullptr) args.tr_price[at] = price;
+        if (args.tr_vol != nullptr) args.tr_vol[at] = vol;
+    }
+};
+
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 
 // ------------------------------------------------------------------------------------------
@@ -473,8 +498,11 @@ struct OrderCtx {
     bool mid;
 };
 
-// FULL: the code may meet mid-price markets (false compiles the last-tick rules alone).
-template <bool FULL>
+// FULL: what the code may meet: kLastOnly last-tick Philox markets alone, kAnyModel mid-price ones
+// too, kAnyGen SplitMix64 as well.
+constexpr int kLastOnly = 0, kAnyModel = 1, kAnyGen = 2;
+
+template <int FULL>
 __device__ __forceinline__ OrderCtx order_ctx(const DevMarket &d, uint32_t s, const Refs &r)
 {
     OrderCtx o;
@@ -534,7 +562,7 @@ __device__ __forceinline__ uint32_t mid_noise_word(const OrderCtx &o, uint32_t w
 }
 
 // MOMENTUM (a < mom_end) or MAKER agent a, either model.
-template <bool FULL>
+template <int FULL>
 __device__ __forceinline__ uint32_t other_word(const OrderCtx &o, uint32_t a, uint32_t w0, uint32_t w3)
 {
     // tick = bid tick + sell x (ask tick - bid tick), written as arithmetic so that the four
@@ -560,7 +588,7 @@ __device__ __forceinline__ void row_words(const Gen &gen, uint32_t b, uint32_t t
     else gen.words4(b + t, w0, w1, w2, w3);
 }
 
-template <bool FULL, bool POW2, typename Gen>
+template <int FULL, bool POW2, typename Gen>
 __device__ __forceinline__ void gen_with(const DevMarket &d, const OrderCtx &o, const Gen &gen, uint32_t t,
                                          uint32_t nthr, uint32_t *bk)
 {
@@ -596,13 +624,13 @@ __device__ __forceinline__ void gen_with(const DevMarket &d, const OrderCtx &o, 
     }
 }
 
-template <bool FULL, bool POW2 = true>
+template <int FULL, bool POW2 = true>
 __device__ __forceinline__ void gen_orders(const DevMarket &d, uint32_t m, uint32_t s, const Refs &r,
                                            uint32_t key0, uint32_t key1, uint32_t t, uint32_t nthr,
                                            uint32_t *bk)
 {
     const OrderCtx o = order_ctx<FULL>(d, s, r);
-    if (FULL && uses_splitmix(d)) {
+    if (FULL >= kAnyGen && uses_splitmix(d)) {
         gen_with<FULL, POW2>(d, o, SplitMixStep(s, m, d.A, ((uint64_t)key1 << 32) | key0), t, nthr, bk);
         return;
     }
@@ -741,6 +769,65 @@ __device__ __forceinline__ void flush_rel_lanes(const FlushLanes &f, uint32_t sp
     if (lane < span + 2u) P[lane] = make_uint2(0u, 0u);
 }
 
+// The one-pass flush for ensembles that may hold either model (see run_market_ovl_any), without
+// branches as flush_rel_lanes: a lane's tick is dt + (n & rel) + (e & de) for the reference
+// n + e / 2 (last-tick markets: n = last, e = 0).  960 mid-price markets (L = 128, A = 256, K = 8,
+// mixed classes), us per step on two / four waves: flush_rel_mid and one generator chain per wave
+// 1.41 / 1.30, this flush and two chains 1.13 / 1.08; one wave per market 1.32.
+struct FlushLanesAny {
+    FlushLanes f;
+    uint32_t rel, de;  // ~0: relative to the reference; 1: half a tick up moves the lane one up
+    uint32_t pairs;    // bin pairs
+    bool one_pass;
+};
+
+__device__ __forceinline__ FlushLanesAny flush_lanes_any(const DevMarket &d, bool mid, uint32_t lane)
+{
+    FlushLanesAny a;
+    if (!mid) {
+        a.f = flush_lanes(d, lane);
+        a.rel = vword(~0u);
+        a.de = vword(0u);
+        a.pairs = 2u * d.K + 3u;
+        a.one_pass = a.pairs + 2u <= 64u;
+        return a;
+    }
+    // as flush_rel_mid: lanes j < np a noise pair each, then the eight extra lanes
+    const uint32_t np = 2u * (2u * d.K + 1u), x = lane - np;
+    const bool noise = lane < np, extra = !noise && x < 8u;
+    const int h = (int)d.h;
+    a.f.pj = noise ? lane : np + min(x >> 1, 3u);
+    a.f.dt = noise ? (int)(lane >> 1) - (int)d.K
+             : !extra ? (int)lane
+             : x == 0u || x == 4u ? (int)d.L - 1
+             : x == 1u || x == 5u ? 0
+             : x == 2u ? 1 : x == 3u ? -1 : x == 6u ? -h : h;
+    a.rel = vword(noise || (extra && (x & 2u)) ? ~0u : 0u);
+    a.de = vword(noise ? 1u - (lane & 1u) : (extra && (x & 2u) ? 1u : 0u));
+    a.f.bx = vword(noise || (extra && (x == 0u || x == 6u)) ? ~0u : 0u);
+    a.f.ay = vword(noise || (extra && (x == 1u || x == 7u)) ? ~0u : 0u);
+    a.f.mb = vword(extra && (x == 2u || x == 4u) ? ~0u : 0u);
+    a.f.ms = vword(extra && (x == 3u || x == 5u) ? ~0u : 0u);
+    a.pairs = np + 4u;
+    a.one_pass = np + 8u <= 64u;
+    return a;
+}
+
+__device__ __forceinline__ void flush_any_lanes(const FlushLanesAny &a, int top, uint32_t ref2, bool rose, bool fell,
+                                                uint32_t *H, uint32_t *bk, uint32_t lane)
+{
+    const FlushLanes &f = a.f;
+    const uint32_t up = rose ? ~0u : 0u, dn = fell ? ~0u : 0u, flat = ~(up | dn);
+    uint2 *P = reinterpret_cast<uint2 *>(H);
+    const uint2 v = P[f.pj];
+    const uint32_t lo = (v.x & (f.bx | (f.mb & (up | flat)))) + (v.y & f.mb & up);
+    const uint32_t hi = (v.x & f.ms & dn) + (v.y & (f.ay | (f.ms & (dn | flat))));
+    const int tick = clamp_tick(f.dt + (int)((ref2 >> 1) & a.rel) + (int)(ref2 & a.de), top);
+    atomicAdd(reinterpret_cast<unsigned long long *>(bk) + tick, ((unsigned long long)hi << 32) | lo);
+    // after the reads (one wave's LDS accesses execute in order)
+    if (lane < a.pairs) P[lane] = make_uint2(0u, 0u);
+}
+
 // Mid-price orders of step s aggregated before the reference 2 mid = 2n + e is known.  A NOISE
 // order's tick floor(mid + K (2 w1 / 2^32 - 1) + 1/2) is n - K + g + c for e = 0 and
 // n - K + g + 1 for e = 1, with g = hi(2K w1) and c = [lo(2K w1) >= 2^31]; it is binned by
@@ -754,24 +841,27 @@ __device__ __forceinline__ void gen_rel_mid(const DevMarket &d, uint32_t s, cons
     const uint32_t twoK = 2u * d.K, xb = 2u * (2u * twoK + 2u);  // first extra pair, in words
     const uint32_t tmkt = (d.flags >> CAE_PMKT_SHIFT) << CAE_PMKT_SHIFT;
     const uint32_t mom_end = d.n_noise + d.n_mom;
-    for (uint32_t b = b0; b < end; b += stride) {
-        const uint32_t a = b | lane;
-        if (a < end) {
-            uint32_t w0, w1, w2, w3;
-            gen.words4_row(b, lane, w0, w1, w2, w3);
-            const uint32_t side = w0 >> 31;
-            const bool mkt = w3 < tmkt;
-            uint32_t word;
-            if (a < d.n_noise) {
-                const uint64_t x = (uint64_t)twoK * w1;
-                const uint32_t c = (uint32_t)x >> 31, u = (uint32_t)(x >> 32) + c;
-                word = mkt ? xb + side : 2u * (2u * u + c) + side;
-            } else if (a < mom_end) {
-                word = xb + (mkt ? 4u : 2u) + side;
-            } else {
-                word = xb + 6u + ((a ^ s) & 1u);
-            }
-            atomicAdd(&H[word], qty1(w2, d.Q));
+    auto place = [&](uint32_t a, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+        const uint32_t side = w0 >> 31;
+        const bool mkt = w3 < tmkt;
+        const uint64_t x = (uint64_t)twoK * w1;
+        const uint32_t c = (uint32_t)x >> 31, u = (uint32_t)(x >> 32) + c;
+        const uint32_t noise = mkt ? xb + side : 2u * (2u * u + c) + side;
+        const uint32_t mom = xb + (mkt ? 4u : 2u) + side;
+        const uint32_t word = a < d.n_noise ? noise : (a < mom_end ? mom : xb + 6u + ((a ^ s) & 1u));
+        if (a < end) atomicAdd(&H[word], qty1(w2, d.Q));
+    };
+    // two rows per pass: two independent generator chains for the wave to issue from (with the
+    // one-pass flush: see flush_lanes_any)
+    for (uint32_t b = b0; b < end; b += 2u * stride) {
+        uint32_t w0, w1, w2, w3, x0, x1, x2, x3;
+        gen.words4_row(b, lane, w0, w1, w2, w3);
+        if (b + stride < end) {
+            gen.words4_row(b + stride, lane, x0, x1, x2, x3);
+            place(b | lane, w0, w1, w2, w3);
+            place((b + stride) | lane, x0, x1, x2, x3);
+        } else {
+            place(b | lane, w0, w1, w2, w3);
         }
     }
 }
@@ -877,7 +967,7 @@ __device__ __forceinline__ void stats_to_lds(uint32_t *scr, const uint32_t *cob,
     }
 }
 
-template <int TPL_MAX, bool MULTI, bool FULL, bool TRACE>
+template <int TPL_MAX, bool MULTI, int FULL, bool TRACE>
 __device__ __forceinline__ void run_market(const EngineArgs &args, const Item &item, uint32_t sub,
                                            uint32_t w_in, uint32_t lane, bool active,
                                            uint32_t *lds)
@@ -934,7 +1024,7 @@ __device__ __forceinline__ void run_market(const EngineArgs &args, const Item &i
         book_ends(bk, d.tpl, lane, bb, ba);
         mid2 = next_mid2(true, bb, ba, last);
     }
-    if constexpr (FULL && MULTI) __syncthreads();  // every wave has read the book before orders land
+    if constexpr (FULL != kLastOnly && MULTI) __syncthreads();  // every wave has read the book before orders land
 
     const double *lnT = args.lnT + d.L;  // ln(L + tick)
     // The log return of step i is added at the end of step i + 1: the table load for the price
@@ -945,6 +1035,7 @@ __device__ __forceinline__ void run_market(const EngineArgs &args, const Item &i
     if constexpr (!kLazy) {
         if (active) ln_prev = lnT[last];
     }
+    [[maybe_unused]] TraceBuf tb;
     for (uint32_t i = 0; i < args.S; ++i) {
         const uint32_t s = (uint32_t)steps0 + i;
         double ln_cur = 0.0;
@@ -1001,7 +1092,10 @@ __device__ __forceinline__ void run_market(const EngineArgs &args, const Item &i
             mid2p = mid2;
             mid2 = next_mid2(mid, co.bb, co.ba, last);
             if constexpr (TRACE) {
-                if (t == 0) trace_step(args, m, i, last, co.v);
+                if (w_in == 0u) {
+                    tb.add(i & 63u, last, co.v, lane);
+                    if ((i & 63u) == 63u || i + 1u == args.S) tb.store(args, m, i & ~63u, (i & 63u) + 1u, lane);
+                }
             }
         }
     }
@@ -1112,7 +1206,7 @@ __device__ __forceinline__ void run_market_ovl(const EngineArgs &args, const Ite
         for (uint32_t q = t; q < 2u * item.hwords; q += nthr) H0[q] = 0u;
     }
     __syncthreads();
-    if (active) gen_orders<false>(d, d.id, (uint32_t)steps0, Refs{last, prev, 2u * last, 0u}, args.k0, args.k1, t,
+    if (active) gen_orders<kLastOnly>(d, d.id, (uint32_t)steps0, Refs{last, prev, 2u * last, 0u}, args.k0, args.k1, t,
                                   nthr, bk);
     __syncthreads();
 
@@ -1123,6 +1217,7 @@ __device__ __forceinline__ void run_market_ovl(const EngineArgs &args, const Ite
     // at most kOvlBlock (L - 1)
     uint32_t b_trade = 0, b_vol = 0, b_px = 0, b_spread = 0, b_nspread = 0;
     double ln_cur = 0.0;  // ln(L + last) on the clearing wave
+    [[maybe_unused]] TraceBuf tb;
     const uint32_t own = min(d.A, item.share * 64u);        // agents of the clearing wave
     const uint32_t ostride = nthr - 64u;                   // the other waves' stride
     const uint32_t span = 2u * d.K + 1u;
@@ -1163,9 +1258,7 @@ __device__ __forceinline__ void run_market_ovl(const EngineArgs &args, const Ite
             ref2 = 2u * last;
             prev = last;
             if (traded) last = co.p;
-            if constexpr (TRACE) {
-                if (lane == 0) trace_step(args, m, i, last, co.v);
-            }
+            if constexpr (TRACE) tb.add(i & (kOvlBlock - 1u), last, co.v, lane);
             // the log-table load is issued here and consumed after the wave's rows
             const double ln_new = lnT[last];
             if (more) gen_rel(d, s + 1u, PhiloxStep(s + 1u, d.id, args.k0, args.k1), 0u, 64u, own, lane, Hn);
@@ -1174,6 +1267,7 @@ __device__ __forceinline__ void run_market_ovl(const EngineArgs &args, const Ite
             sum_r2 = sum_r2 + x * x;
             ln_cur = ln_new;
             if (((i + 1u) & (kOvlBlock - 1u)) == 0u || !more) {  // hand over (or finish)
+                if constexpr (TRACE) tb.store(args, m, i & ~(kOvlBlock - 1u), (i & (kOvlBlock - 1u)) + 1u, lane);
                 if (lane == 0) {
                     *reinterpret_cast<uint4 *>(scr) = make_uint4(last, prev, ref2, 0u);
                     fs[0] = sum_r;
@@ -1237,7 +1331,7 @@ __device__ __forceinline__ void run_market_ovl(const EngineArgs &args, const Ite
 // The same schedule for ensembles that may hold mid-price or SplitMix64 markets (the FULL
 // instantiation): the reference is 2 x mid, tracked as in run_market, and the bins are the
 // model's (gen_rel / gen_rel_mid).  Scratch words 2 and 3 hand over mid2 and mid2p.
-template <int TPL_MAX, bool FULL, bool TRACE>
+template <int TPL_MAX, int FULL, bool TRACE>
 __device__ __forceinline__ void run_market_ovl_any(const EngineArgs &args, const Item &item, uint32_t sub,
                                                uint32_t w_in, uint32_t lane, bool active, uint32_t *lds)
 {
@@ -1280,14 +1374,14 @@ __device__ __forceinline__ void run_market_ovl_any(const EngineArgs &args, const
     }
     __syncthreads();
     const bool mid = FULL && (d.flags & CAE_MODEL_MASK) == CAE_MODEL_MID;
-    const bool smx = FULL && uses_splitmix(d);
+    const bool smx = FULL >= kAnyGen && uses_splitmix(d);
     mid2 = 2u * last;
     if (FULL && active && mid) {
         uint32_t bb, ba;
         book_ends(bk, d.tpl, lane, bb, ba);
         mid2 = next_mid2(true, bb, ba, last);
     }
-    if constexpr (FULL) __syncthreads();  // every wave has read the book before orders land
+    if constexpr (FULL != kLastOnly) __syncthreads();  // every wave has read the book before orders land
     if (active) gen_orders<FULL>(d, d.id, (uint32_t)steps0, Refs{last, prev, mid2, mid2p}, args.k0, args.k1, t,
                                  nthr, bk);
     __syncthreads();
@@ -1296,7 +1390,7 @@ __device__ __forceinline__ void run_market_ovl_any(const EngineArgs &args, const
     const uint64_t seed64 = ((uint64_t)args.k1 << 32) | args.k0;
     // the next step's orders into bin buffer Hn, agents b | lane for b = b0, b0 + stride, ...
     const auto gen_bins = [&](uint32_t sn, uint32_t b0, uint32_t stride, uint32_t end, uint32_t *Hn) {
-        if constexpr (FULL) {
+        if constexpr (FULL != kLastOnly) {
             if (smx) {
                 const SplitMixStep g(sn, d.id, d.A, seed64);
                 if (mid) gen_rel_mid(d, sn, g, b0, stride, end, lane, Hn);
@@ -1310,6 +1404,8 @@ __device__ __forceinline__ void run_market_ovl_any(const EngineArgs &args, const
         }
         gen_rel(d, sn, PhiloxStep(sn, d.id, args.k0, args.k1), b0, stride, end, lane, Hn);
     };
+    [[maybe_unused]] TraceBuf tb;
+    const FlushLanesAny fl = flush_lanes_any(d, mid, lane);
     uint64_t n_trade = 0, sum_vol = 0, sum_px = 0, sum_spread = 0, n_spread = 0;  // this wave's steps
     const uint32_t own = min(d.A, item.share * 64u);        // agents of the clearing wave
     const uint32_t ostride = nthr - 64u;                   // the other waves' stride
@@ -1330,7 +1426,10 @@ __device__ __forceinline__ void run_market_ovl_any(const EngineArgs &args, const
                 sum_r2 = fs[1];
             }
             if (i >= 1u) {
-                if (FULL && mid) flush_rel_mid(d, mid2, mid2p, (i & 1u) ? H1 : H0, bk, lane);
+                if (fl.one_pass)
+                    flush_any_lanes(fl, (int)d.L - 1, mid ? mid2 : 2u * last, mid ? mid2 > mid2p : last > prev,
+                                    mid ? mid2 < mid2p : last < prev, (i & 1u) ? H1 : H0, bk, lane);
+                else if (FULL && mid) flush_rel_mid(d, mid2, mid2p, (i & 1u) ? H1 : H0, bk, lane);
                 else flush_rel(d, last, prev, (i & 1u) ? H1 : H0, bk, lane);
             }
             wave_sync();
@@ -1348,15 +1447,14 @@ __device__ __forceinline__ void run_market_ovl_any(const EngineArgs &args, const
             if (co.v != 0) last = co.p;
             mid2p = mid2;
             mid2 = next_mid2(mid, co.bb, co.ba, last);
-            if constexpr (TRACE) {
-                if (lane == 0) trace_step(args, m, i, last, co.v);
-            }
+            if constexpr (TRACE) tb.add(i & (kOvlBlock - 1u), last, co.v, lane);
             // the log-table loads are issued here and consumed after the wave's rows
             const double x = lnT[last] - lnT[prev];
             if (more) gen_bins(s + 1u, 0u, 64u, own, Hn);
             sum_r = sum_r + x;
             sum_r2 = sum_r2 + x * x;
             if (((i + 1u) & (kOvlBlock - 1u)) == 0u || !more) {  // hand over (or finish)
+                if constexpr (TRACE) tb.store(args, m, i & ~(kOvlBlock - 1u), (i & (kOvlBlock - 1u)) + 1u, lane);
                 if (lane == 0) {
                     *reinterpret_cast<uint4 *>(scr) = make_uint4(last, prev, mid2, mid2p);
                     fs[0] = sum_r;
@@ -1430,7 +1528,7 @@ __device__ __forceinline__ void st_u64(uint32_t *p, uint64_t v)
 // G-1 waves generate and aggregate the other market's orders.  One barrier per phase; no wave
 // waits for a clearing.  With one market the phases alternate between its orders and its
 // clearing.  Phase count: 2S (+1 to clear B's last step).
-template <int TPL_MAX, bool FULL, bool TRACE>
+template <int TPL_MAX, int FULL, bool TRACE>
 __device__ __forceinline__ void run_pair(const EngineArgs &args, const Item &item, uint32_t wave, uint32_t lane,
                                          uint32_t G, uint32_t *lds)
 {
@@ -1882,9 +1980,9 @@ __device__ __forceinline__ void run_packed_seg(const EngineArgs &args, const Ite
         const uint32_t s = s0 + i;
         const double ln_cur = (active && i >= 1u) ? lnT[last] : 0.0;
         {
-            const OrderCtx o = order_ctx<false>(d, s, Refs{last, prev, 2u * last, 0u});
+            const OrderCtx o = order_ctx<kLastOnly>(d, s, Refs{last, prev, 2u * last, 0u});
             if (row0) {
-                const uint32_t w = ll >= o.n_noise ? other_word<false>(o, ll, pw0, pw3) : noise_word(o, pw0, pw1);
+                const uint32_t w = ll >= o.n_noise ? other_word<kLastOnly>(o, ll, pw0, pw3) : noise_word(o, pw0, pw1);
                 atomicAdd(&bk[pad_word(w)], order_qty(o, pw2));
             }
             // further rows of SEG agents until every segment's market is done (the markets of a
@@ -1901,18 +1999,18 @@ __device__ __forceinline__ void run_packed_seg(const EngineArgs &args, const Ite
                         gen.words4(a, w0, w1, w2, w3);
                         gen.words4(a2, v0, v1, v2, v3);
                         if (on) {
-                            const uint32_t w = a >= o.n_noise ? other_word<false>(o, a, w0, w3) : noise_word(o, w0, w1);
+                            const uint32_t w = a >= o.n_noise ? other_word<kLastOnly>(o, a, w0, w3) : noise_word(o, w0, w1);
                             atomicAdd(&bk[pad_word(w)], order_qty(o, w2));
                         }
                         if (on2) {
-                            const uint32_t w = a2 >= o.n_noise ? other_word<false>(o, a2, v0, v3) : noise_word(o, v0, v1);
+                            const uint32_t w = a2 >= o.n_noise ? other_word<kLastOnly>(o, a2, v0, v3) : noise_word(o, v0, v1);
                             atomicAdd(&bk[pad_word(w)], order_qty(o, v2));
                         }
                     } else {
                         if (on) {
                             uint32_t w0, w1, w2, w3 = 0;
                             gen.words4(a, w0, w1, w2, w3);
-                            const uint32_t w = a >= o.n_noise ? other_word<false>(o, a, w0, w3) : noise_word(o, w0, w1);
+                            const uint32_t w = a >= o.n_noise ? other_word<kLastOnly>(o, a, w0, w3) : noise_word(o, w0, w1);
                             atomicAdd(&bk[pad_word(w)], order_qty(o, w2));
                         }
                         break;
@@ -1983,11 +2081,11 @@ __device__ __forceinline__ void run_packed(const EngineArgs &args, const Item &i
     else run_packed_seg<5, TRACE>(args, item, wave, lane, lds);
 }
 
-// FULL: some market may use the mid-price model; TRACE: record the per-step series; PACK: some
+// FULL: the models and generators the markets may use (kLastOnly ..); TRACE: record the per-step series; PACK: some
 // items hold packed small markets (their per-lane generator and clearing need more vector
 // registers, so only ensembles that use them run this code).  Each instantiation carries only
 // the code it needs, which keeps registers for the step loop.
-template <int TPL_MAX, bool FULL, bool TRACE, bool PACK>
+template <int TPL_MAX, int FULL, bool TRACE, bool PACK>
 __global__ void __launch_bounds__(1024) cae_engine_kernel(const EngineArgs args)
 {
     extern __shared__ __align__(16) uint32_t lds[];
@@ -2015,7 +2113,7 @@ __global__ void __launch_bounds__(1024) cae_engine_kernel(const EngineArgs args)
         } else if (item.wpm_log2 == 0) {
             if (active) run_market<TPL_MAX, false, FULL, TRACE>(args, item, sub, w_in, lane, true, lds);
         } else if (item.pipe == 2u) {
-            if constexpr (FULL) run_market_ovl_any<TPL_MAX, true, TRACE>(args, item, sub, w_in, lane, active, lds);
+            if constexpr (FULL != kLastOnly) run_market_ovl_any<TPL_MAX, FULL, TRACE>(args, item, sub, w_in, lane, active, lds);
             else run_market_ovl<TPL_MAX, TRACE>(args, item, sub, w_in, lane, active, lds);
         } else {
             run_market<TPL_MAX, true, FULL, TRACE>(args, item, sub, w_in, lane, active, lds);
@@ -2069,12 +2167,12 @@ __global__ void __launch_bounds__(64) cae_naive_kernel(const EngineArgs args, ui
         const PhiloxStep ph(s, d.id, args.k0, args.k1);
         const SplitMixStep sm(s, d.id, d.A, ((uint64_t)args.k1 << 32) | args.k0);
         const bool smx = uses_splitmix(d);
-        const OrderCtx o = order_ctx<true>(d, s, Refs{st.last, st.prev, mid2, mid2p});
+        const OrderCtx o = order_ctx<kAnyGen>(d, s, Refs{st.last, st.prev, mid2, mid2p});
         for (uint32_t a = 0; a < d.A; ++a) {
             uint32_t w0, w1, w2, w3;
             if (smx) sm.words4(a, w0, w1, w2, w3);
             else ph.words4(a, w0, w1, w2, w3);
-            const uint32_t w = a >= d.n_noise ? other_word<true>(o, a, w0, w3)
+            const uint32_t w = a >= d.n_noise ? other_word<kAnyGen>(o, a, w0, w3)
                                : mid          ? mid_noise_word(o, w0, w1, w3)
                                               : noise_word(o, w0, w1);
             const uint32_t q = order_qty(o, w2);
@@ -2343,6 +2441,7 @@ uint32_t tpl_for(uint32_t L)
 // Words of one order-bin buffer of an overlapped market: 2K + 3 (bid, ask) pairs, rounded up to
 // a power of two of at least 64 so that markets of nearby K share items.
 constexpr uint32_t kMaxOverlapK = 1022, kMaxOverlapKMid = 510;
+constexpr uint32_t kMidOnePassK = 13;  // 4 K + 10 bins and roles fit the flush's 64 lanes (flush_lanes_any)
 uint32_t hwords_for(uint32_t K, bool mid)
 {
     const uint32_t need = mid ? 8u * K + 12u : 4u * K + 6u;  // last-tick: 2K + 3 pairs; mid: 4K + 6
@@ -2429,7 +2528,7 @@ using EngineFn = void (*)(const EngineArgs);
 // packed instantiations are those of small books).
 constexpr uint32_t kPackMaxL = 128;
 
-template <bool FULL, bool TRACE>
+template <int FULL, bool TRACE>
 EngineFn engine_fn_t(uint32_t tpl_max, bool pack)
 {
     if (pack) return tpl_max <= 1 ? cae_engine_kernel<1, FULL, TRACE, true> : cae_engine_kernel<2, FULL, TRACE, true>;
@@ -2442,12 +2541,14 @@ EngineFn engine_fn_t(uint32_t tpl_max, bool pack)
     }
 }
 
-// The instantiation for the largest book, with mid-price code only when some market uses that
-// model, trace stores only for cae_step_traced and the packed path only when items use it.
-EngineFn engine_fn(uint32_t tpl_max, bool mid, bool trace, bool pack)
+// The instantiation for the largest book, with mid-price or SplitMix64 code only when some market
+// uses that model or generator, trace stores only for cae_step_traced and the packed path only when items use it.
+EngineFn engine_fn(uint32_t tpl_max, int full, bool trace, bool pack)
 {
-    if (mid) return trace ? engine_fn_t<true, true>(tpl_max, pack) : engine_fn_t<true, false>(tpl_max, pack);
-    return trace ? engine_fn_t<false, true>(tpl_max, pack) : engine_fn_t<false, false>(tpl_max, pack);
+    if (full == kAnyGen) return trace ? engine_fn_t<kAnyGen, true>(tpl_max, pack) : engine_fn_t<kAnyGen, false>(tpl_max, pack);
+    if (full == kAnyModel)
+        return trace ? engine_fn_t<kAnyModel, true>(tpl_max, pack) : engine_fn_t<kAnyModel, false>(tpl_max, pack);
+    return trace ? engine_fn_t<kLastOnly, true>(tpl_max, pack) : engine_fn_t<kLastOnly, false>(tpl_max, pack);
 }
 
 // The waves per market that bounds what a caller's waves_per_group may be when it leaves the
@@ -2467,7 +2568,8 @@ struct AutoClass {
 // Schedule of a size class whose waves the caller leaves to the library: tpl ticks per lane, A
 // agents (the class's mean), `full` waves that would spread the chip's 16 waves per CU over the
 // ensemble in proportion to cost (4096 / M for M equal markets on 256 CUs), plain: some market of
-// the class does not run the last-tick Philox model.
+// the class uses SplitMix64, or the mid-price model with more bins than a flush places in one pass
+// (the overlapped schedule does not pay for those); mid: some market uses the mid-price model.
 //   * A market gets its share of the waves, as long as every wave has work: a row of 64 agents
 //     each when the chip is nearly empty (full >= 16), two rows otherwise; few agents or a book
 //     longer than the order flow fill one wave (the clearing is one wave's work whatever the
@@ -2475,28 +2577,36 @@ struct AutoClass {
 //     waves), M = 512 1.8 / 1.10 (8), M = 1024 2.9 / 1.74 (4), M = 4096 6.8 / 6.8 (1).
 //   * The next step's orders are generated during the clearing (overlap) where that clearing is
 //     short against them: always for books of up to 4 ticks per lane (M = 1024: 2.08 -> 1.74),
-//     for longer ones only with enough agents (L = 512, A = 512, M = 64: 1.54 with, 1.18 without).
+//     for longer ones only with enough agents (L = 512, A = 512, M = 64: 1.54 with, 1.18 without)
+//     or for the mid-price model, whose orders wait for both best quotes otherwise (L = 512,
+//     A = 1024, K = 8, M = 256: 1.32 with, 1.80 without).  With it, a mid-price market of up to
+//     four rows has use for a wave per row on a fuller chip too (L = 128, A = 256, M = 960: four
+//     waves 1.08, two 1.14, one 1.32; L = 64, A = 128, M = 960: two 0.83, one 0.96), and none for
+//     more than 8 below A = 2048 (L = 256, A = 1024, M = 256: 16 waves 1.09, 8 1.00); beyond
+//     M = 1600 the small ones keep one wave (L = 256, A = 128, M = 2048: two 1.43, one 1.23).
 //     The clearing wave's share of the rows is what its clearing leaves of an even one.
 // Over 300 shapes (L 64..1024, A 16..16384, M 4..8192) the rule is within 1.1 % of the best of the
 // schedules it chooses from, in geometric mean (17 % at most); a rule on A alone lost 15 %.
-AutoClass auto_class(uint32_t tpl, double A, double full, bool plain)
+AutoClass auto_class(uint32_t tpl, double A, double full, bool plain, bool mid)
 {
     const uint32_t rows = (uint32_t)std::ceil(A / 64.0);
     AutoClass c{1u, 0u};
-    if (A <= 128.0) return c;
+    mid = mid && !plain;
+    if (A <= (mid ? 64.0 : 128.0)) return c;
     double cap;
     if (full >= 16.0) {
         cap = rows <= 4u || (!plain && (tpl <= 4u || A >= 2048.0)) ? rows : rows / 2.0;
+        if (mid && A < 2048.0) cap = std::min(cap, 8.0);
     } else {
-        cap = plain ? rows / 4.0 : rows / 2.0;
-        if (tpl >= 8u) cap = std::min(cap, A / (32.0 * tpl));
+        cap = plain ? rows / 4.0 : !mid || rows > 4u ? rows / 2.0 : full >= 2.5 ? rows : 1.0;
+        if (tpl >= 8u && !mid) cap = std::min(cap, A / (32.0 * tpl));
     }
     const double w = std::min({full, cap, 16.0});
     while (2.0 * c.wpm <= w) c.wpm <<= 1;
-    if (c.wpm < 2u || plain || (tpl >= 8u && full >= 16.0 && A < 2048.0)) return c;
+    if (c.wpm < 2u || plain || (tpl >= 8u && !mid && full >= 16.0 && A < 2048.0)) return c;
     const uint32_t even = rows / c.wpm;
     uint32_t share = 0;
-    if (tpl >= 16u || (tpl == 8u && (A < 2048.0 || full >= 8.0))) share = 0;
+    if (tpl >= 16u || (tpl == 8u && ((A < 2048.0 && !(mid && even >= 8u)) || full >= 8.0))) share = 0;
     else if (even >= 8u) share = 3u * even / 4u;
     else if (even >= 3u) share = c.wpm == 4u ? even - 1u : even / 2u;
     c.overlap = share + 1u;
@@ -2548,7 +2658,7 @@ struct cae_ensemble {
     uint64_t book_words = 0;
     Layout lay{};
     uint32_t n_items = 0, tpl_max = 1, waves_per_group = 1, lds_bytes = 0, grid = 0;
-    bool any_mid = false;  // some market uses the mid-price model or the SplitMix64 generator
+    int full = kLastOnly;  // the models and generators its markets use
     bool any_pack = false; // some item holds packed small markets
     cae_tuning tuning{};
     uint32_t timed_groups = 0;  // workgroups of the last launch (0: none yet)
@@ -2570,8 +2680,9 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     std::vector<uint32_t> wpm(M);
     uint32_t wpm_max = 1, tpl_max = 1;
     for (uint32_t m = 0; m < M; ++m)
-        e->any_mid |= (e->desc[m].flags & CAE_MODEL_MASK) == CAE_MODEL_MID ||
-                      ((e->desc[m].flags >> CAE_GEN_SHIFT) & 0xFFu) == CAE_GEN_SPLITMIX;
+        e->full = std::max(e->full, ((e->desc[m].flags >> CAE_GEN_SHIFT) & 0xFFu) == CAE_GEN_SPLITMIX ? kAnyGen
+                                    : (e->desc[m].flags & CAE_MODEL_MASK) == CAE_MODEL_MID            ? kAnyModel
+                                                                                                      : kLastOnly);
     std::vector<uint32_t> packp(M, 0u);
     uint32_t ncu = 0;
     int rc = device_cus(e->device, &ncu);
@@ -2587,7 +2698,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     {
         double cost[CAE_NUM_CLASSES] = {}, agents[CAE_NUM_CLASSES] = {}, total = 0.0, dearest = 0.0;
         uint32_t count[CAE_NUM_CLASSES] = {}, need[CAE_NUM_CLASSES] = {}, A_max = 0;
-        bool plain[CAE_NUM_CLASSES] = {}, all_auto = true, any_plain = false;
+        bool plain[CAE_NUM_CLASSES] = {}, mid[CAE_NUM_CLASSES] = {}, all_auto = true, small_last = maxL <= kPackMaxL;
         for (uint32_t m = 0; m < M; ++m) {
             const cae_market &d = e->desc[m];
             const uint32_t c = lclass(d.L) * 8u + aclass(d.A);
@@ -2596,7 +2707,10 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             cost[c] += w;
             agents[c] += d.A;
             total += w;
-            plain[c] |= (d.flags & 0xFFFFu) != 0u;
+            plain[c] |= ((d.flags >> CAE_GEN_SHIFT) & 0xFFu) != CAE_GEN_PHILOX ||
+                        ((d.flags & CAE_MODEL_MASK) == CAE_MODEL_MID && d.K > kMidOnePassK);
+            mid[c] |= (d.flags & CAE_MODEL_MASK) == CAE_MODEL_MID;
+            small_last = small_last && (d.flags & 0xFFFFu) == 0u;
             need[c] = std::max(need[c], auto_wpm(d.A));
             A_max = std::max(A_max, d.A);
         }
@@ -2604,10 +2718,9 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             if (!count[c]) continue;
             auto_c[c] = t.waves_per_market[c] == 0 && t.pipelined[c] == 0 && t.pack[c] == 0;
             all_auto = all_auto && auto_c[c] && t.overlap[c] == 0;
-            any_plain |= plain[c];
             dearest = std::max(dearest, cost[c] / count[c]);
         }
-        const uint32_t P = all_auto && !any_plain && maxL <= kPackMaxL ? auto_pack(A_max, (double)M / ncu) : 0u;
+        const uint32_t P = all_auto && small_last ? auto_pack(A_max, (double)M / ncu) : 0u;
         for (uint32_t c = 0; c < CAE_NUM_CLASSES; ++c) {
             if (!count[c] || !auto_c[c]) continue;
             if (P) {
@@ -2618,7 +2731,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             const double A = agents[c] / count[c];
             AutoClass a = dearest > 1.5 * total / M
                               ? auto_class_mixed(A, full, 16.0 * ncu * dearest / total, plain[c])
-                              : auto_class(1u << (c / 8u), A, full, plain[c]);
+                              : auto_class(1u << (c / 8u), A, full, plain[c], mid[c]);
             // a caller's group size below what the class's markets need is refused further down
             if (t.waves_per_group && need[c] > t.waves_per_group) a.wpm = need[c];
             while (t.waves_per_group && need[c] <= t.waves_per_group && a.wpm > t.waves_per_group) a.wpm >>= 1;
@@ -2805,7 +2918,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     e->lds_bytes = lds_max;
 
     int per_cu = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(engine_fn(tpl_max, e->any_mid, false, e->any_pack)),
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(engine_fn(tpl_max, e->full, false, e->any_pack)),
                                                          (int)(G * 64u), (size_t)lds_max));
     if (per_cu < 1) return fail(CAE_EINVAL, "schedule does not fit on a CU (lds %u B, %u waves)", lds_max, G);
     if (t.groups_per_cu) per_cu = std::min<int>(per_cu, (int)t.groups_per_cu);
@@ -2966,7 +3079,7 @@ static int step_impl(cae_ensemble *e, uint32_t S, bool naive, uint32_t *tr_price
     if (naive)
         hipLaunchKernelGGL(cae_naive_kernel, dim3((e->M + 63u) / 64u), dim3(64), 0, e->stream, a, e->M);
     else
-        hipLaunchKernelGGL(engine_fn(e->tpl_max, e->any_mid, tr_price != nullptr || tr_vol != nullptr, e->any_pack),
+        hipLaunchKernelGGL(engine_fn(e->tpl_max, e->full, tr_price != nullptr || tr_vol != nullptr, e->any_pack),
                            dim3(e->grid), dim3(e->waves_per_group * 64u), e->lds_bytes,
                            e->stream, a);
     HIP_TRY(hipGetLastError());
