@@ -555,7 +555,7 @@ def main():
     roof = {"bound": "alu" if valu_ceiling(L, A) <= lds_ceiling(L, A) else "lds",
             "achieved": achieved / 1e12, "peak": PEAK_SLOTS / 1e12,
             "unit": "TOP/s", "frac": achieved / PEAK_SLOTS, "traffic": measured_traffic(),
-            "kernel": "cae_engine_kernel<%d,false,false,false>" % max(1, L // 64), "kernel_ms": kms,
+            "kernel": "cae_engine_kernel<%d,0,false,false>" % max(1, L // 64), "kernel_ms": kms,
             "kernel_ms_last_launch": min(last_ms), "slots_per_event": round(w_ev, 3),
             "lds": {"frac": lds_busy, "ceiling_events_per_s": lds_ceiling(L, A),
                     "clocks_per_event": lds_clocks_per_event(L, A)},
