@@ -837,7 +837,7 @@ __device__ __forceinline__ void flush_any_lanes(const FlushLanesAny &a, int top,
 // PAIR generates two rows per pass, without branches: two independent generator chains for the
 // wave to issue from, where a row yields its four words together (Philox).  SplitMix64 mixes each
 // word by itself, so there the words a rule does not use are skipped by branching (four waves, L =
-// 256, A = 2000, M = 600, us per step: 5.2 in pairs, 4.8 so).
+// 256, A = 2000, M = 600, us per step: 5.2 in pairs, 4.7 so).
 template <bool PAIR, typename Gen>
 __device__ __forceinline__ void gen_rel_mid(const DevMarket &d, uint32_t s, const Gen &gen, uint32_t b0,
                                             uint32_t stride, uint32_t end, uint32_t lane, uint32_t *H)

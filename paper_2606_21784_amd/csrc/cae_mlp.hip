@@ -1040,16 +1040,16 @@ __global__ void __launch_bounds__(kPredThreads) mlp_predict(const PredArgs a)
 // Fused training step: forward, loss gradient, back-propagation and Adam in two launches, on
 // gfx950's v_mfma_f32_16x16x32_bf16 (eight bfloat16 of the reduction per lane and operand).
 //
-// mlp_train_rows: one workgroup per 16 batch rows.  The rows' input, both hidden activations,
-//   their pre-activations, the loss gradient and the first back-propagated gradient stay in LDS;
-//   every operand fragment is one 16-byte read (LDS rows, the bfloat16 W2 and its transposed
-//   copy).  The activations and gradients the weight gradients need are written to the
+// mlp_train_rows: one workgroup per 16 batch rows.  The rows' input, both hidden activations, the
+//   loss gradient and the first back-propagated gradient stay in LDS, the pre-activations in
+//   registers; every operand fragment is one 16-byte read (LDS rows, the bfloat16 W2 and its
+//   transposed copy).  The activations and gradients the weight gradients need are written to the
 //   workspace transposed ([feature][batch], 8-byte stores), so that the next kernel reads its
 //   fragments (eight consecutive batch rows) with 16-byte loads as well.
-// mlp_train_params: one wave per 16x16 tile of a weight gradient (with the bias as the extra row
-//   of ones, as in the unfused path), reduced over the whole batch in a fixed order by the wave
-//   that owns it -- no split-K partials, deterministic -- followed in the same wave by Adam and
-//   the bfloat16 copies of the updated weights.
+// mlp_train_params: four waves per 16x16 tile of a weight gradient (with the bias as the extra row
+//   of ones, as in the unfused path), each reducing an interleaved quarter of the batch; their sums
+//   are added in a fixed order -- deterministic -- and each wave then applies Adam to a quarter of
+//   the tile and stores the bfloat16 copies of the updated weights.
 // Rounding points and fp32 accumulation are those of the unfused kernels; only the order of the
 // fp32 sums differs.
 // ------------------------------------------------------------------------------------------
