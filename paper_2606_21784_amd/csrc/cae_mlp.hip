@@ -1772,13 +1772,15 @@ int cae_mlp_loss_grad(const float *y, const float *target, float *dy, float *los
     if (n == 0) return mfail(CAE_EINVAL, "n must be >= 1");
     if (kind != CAE_LOSS_MSE && kind != CAE_LOSS_HUBER) return mfail(CAE_EINVAL, "unknown loss kind");
     if (kind == CAE_LOSS_HUBER && !(delta > 0.0f)) return mfail(CAE_EINVAL, "Huber delta must be > 0");
-    // the gradient in workgroups of its own, unless it is short or overwrites an input that
-    // workgroup 0 may still read
-    const auto apart = [n](const void *a, const void *b, size_t nb) {
+    // the gradient in workgroups of its own, unless it is short, or it or the loss overwrites words
+    // that another workgroup reads or writes
+    const size_t nb = 4u * (size_t)n;
+    const auto apart = [](const void *a, size_t na, const void *b, size_t nb) {
         const uintptr_t x = reinterpret_cast<uintptr_t>(a), z = reinterpret_cast<uintptr_t>(b);
-        return x + 4u * (size_t)n <= z || z + nb <= x;
+        return x + na <= z || z + nb <= x;
     };
-    const bool split = n > 2u * kLossThreads && apart(dy, y, 4u * (size_t)n) && apart(dy, target, 4u * (size_t)n);
+    const bool split = n > 2u * kLossThreads && apart(dy, nb, y, nb) && apart(dy, nb, target, nb) &&
+                       apart(loss, 4u, y, nb) && apart(loss, 4u, target, nb) && apart(loss, 4u, dy, nb);
     const uint32_t blocks = split ? 1u + std::min<uint32_t>((n + kLossThreads - 1u) / kLossThreads, 512u) : 1u;
     hipLaunchKernelGGL(loss_grad, dim3(blocks), dim3(kLossThreads), 0, (hipStream_t)stream, y, target, dy, loss, n,
                        kind, delta);
