@@ -2718,12 +2718,13 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     uint32_t maxL = 0;
     for (uint32_t m = 0; m < M; ++m) maxL = std::max(maxL, e->desc[m].L);
     e->any_pack = false;
+    const uint32_t lds_budget = std::min(t.max_lds_bytes ? t.max_lds_bytes : 64u * 1024u, 160u * 1024u);
     // the classes left to the library (no waves, mode or packing given): one schedule per class,
     // from its share of the ensemble's cost
-    bool auto_c[CAE_NUM_CLASSES] = {}, auto_ov[CAE_NUM_CLASSES] = {};
+    bool auto_c[CAE_NUM_CLASSES] = {};
     {
         double cost[CAE_NUM_CLASSES] = {}, agents[CAE_NUM_CLASSES] = {}, total = 0.0, dearest = 0.0;
-        uint32_t count[CAE_NUM_CLASSES] = {}, need[CAE_NUM_CLASSES] = {}, A_max = 0;
+        uint32_t count[CAE_NUM_CLASSES] = {}, need[CAE_NUM_CLASSES] = {}, bins[CAE_NUM_CLASSES] = {}, A_max = 0;
         bool plain[CAE_NUM_CLASSES] = {}, mid[CAE_NUM_CLASSES] = {}, all_auto = true, small_last = maxL <= kPackMaxL;
         for (uint32_t m = 0; m < M; ++m) {
             const cae_market &d = e->desc[m];
@@ -2738,6 +2739,8 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             mid[c] |= (d.flags & CAE_MODEL_MASK) == CAE_MODEL_MID;
             small_last = small_last && (d.flags & 0xFFFFu) == 0u;
             need[c] = std::max(need[c], auto_wpm(d.A));
+            const bool mid_m = (d.flags & CAE_MODEL_MASK) == CAE_MODEL_MID;
+            if (d.K <= (mid_m ? kMaxOverlapKMid : kMaxOverlapK)) bins[c] = std::max(bins[c], hwords_for(d.K, mid_m));
             A_max = std::max(A_max, d.A);
         }
         for (uint32_t c = 0; c < CAE_NUM_CLASSES; ++c) {
@@ -2762,10 +2765,10 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             if (t.waves_per_group && need[c] > t.waves_per_group) a.wpm = need[c];
             while (t.waves_per_group && need[c] <= t.waves_per_group && a.wpm > t.waves_per_group) a.wpm >>= 1;
             t.waves_per_market[c] = (uint8_t)a.wpm;
-            if (t.overlap[c] == 0 && a.wpm >= 2u) {
-                t.overlap[c] = (uint8_t)std::min(a.overlap, 255u);
-                auto_ov[c] = true;
-            }
+            // (every overlapped market's bins have to fit a caller's LDS budget, so that the schedule
+            // reported is the one in use and keeps to the budget when it is passed back)
+            const bool fits = bins[c] && 4u * (2u * 64u * (1u << (c / 8u)) + 2u * bins[c] + kScr) <= lds_budget;
+            if (t.overlap[c] == 0 && a.wpm >= 2u && fits) t.overlap[c] = (uint8_t)std::min(a.overlap, 255u);
         }
     }
     for (uint32_t m = 0; m < M; ++m) {
@@ -2804,8 +2807,6 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     bool any_pipe = false;
     for (uint32_t c = 0; c < CAE_NUM_CLASSES; ++c) any_pipe |= t.pipelined[c] != 0;
     if (any_pipe && G < 2) return fail(CAE_EINVAL, "pipelined classes need waves_per_group >= 2");
-    uint32_t lds_budget = t.max_lds_bytes ? t.max_lds_bytes : 64u * 1024u;
-    if (lds_budget > 160u * 1024u) lds_budget = 160u * 1024u;
 
     // LPT cost of one market-step: measured per class if given, else agent work plus the
     // clearing wave's pass over 64*tpl ticks
@@ -2834,9 +2835,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
         const uint32_t c = lclass(e->desc[m].L) * 8u + aclass(e->desc[m].A);
         // overlapped markets keep two buffers of bins in LDS; wider offset ranges run plain
         const bool mid = (e->desc[m].flags & CAE_MODEL_MASK) == CAE_MODEL_MID;
-        uint32_t ov = e->desc[m].K <= (mid ? kMaxOverlapKMid : kMaxOverlapK) ? t.overlap[c] : 0u;
-        // (the bins of a wide offset range may not fit a caller's LDS budget)
-        if (ov && auto_ov[c] && 4u * (2u * 64u * tp + 2u * hwords_for(e->desc[m].K, mid) + kScr) > lds_budget) ov = 0u;
+        const uint32_t ov = e->desc[m].K <= (mid ? kMaxOverlapKMid : kMaxOverlapK) ? t.overlap[c] : 0u;
         uint32_t pp = t.pipelined[c] ? 1u : (ov ? 2u : 0u);
         uint32_t share = ov ? ov - 1u : 0u;
         uint32_t hw = ov ? hwords_for(e->desc[m].K, mid) : 0u;
