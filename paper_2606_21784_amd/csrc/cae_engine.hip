@@ -2476,6 +2476,21 @@ uint32_t hwords_for(uint32_t K, bool mid)
     return w;
 }
 
+// LDS words of one book of L ticks packed P to a wave: hw ticks per lane of its segment, two words
+// per tick plus four of padding per 32 ticks (pad_pair), and the scratch words.
+uint32_t packed_hw(uint32_t L, uint32_t P)
+{
+    uint32_t hw = 1;
+    while (64u / P * hw < L) hw <<= 1;
+    return hw;
+}
+
+uint32_t packed_stride(uint32_t hw, uint32_t P)
+{
+    const uint32_t ticks = 64u / P * hw;
+    return 2u * ticks + 4u * ((ticks + 31u) / 32u) + kScr;
+}
+
 uint32_t lclass(uint32_t L)
 {
     uint32_t c = 0;
@@ -2749,7 +2764,9 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             all_auto = all_auto && auto_c[c] && t.overlap[c] == 0;
             dearest = std::max(dearest, cost[c] / count[c]);
         }
-        const uint32_t P = all_auto && small_last ? auto_pack(A_max, (double)M / ncu) : 0u;
+        // (an item holds LDS for every book of its waves: at least one wave's must fit a caller's budget)
+        uint32_t P = all_auto && small_last ? auto_pack(A_max, (double)M / ncu) : 0u;
+        while (P && 4u * P * packed_stride(packed_hw(maxL, P), P) > lds_budget) P = P == 4u ? 2u : 0u;
         for (uint32_t c = 0; c < CAE_NUM_CLASSES; ++c) {
             if (!count[c] || !auto_c[c]) continue;
             if (P) {
@@ -2842,13 +2859,11 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
         uint32_t stride = 2u * 64u * tp + 2u * hw + kScr;
         uint32_t cap = pp == 1u ? 2u : G / w;
         if (packp[m]) {  // P markets per wave, books of seg * hw ticks (hw ticks per lane)
-            const uint32_t seg = 64u / packp[m];
             pp = 3u;
             share = packp[m];
-            hw = 1u;
-            while (seg * hw < e->desc[m].L) hw <<= 1;
+            hw = packed_hw(e->desc[m].L, packp[m]);
             tp = 0u;
-            stride = 2u * seg * hw + 4u * ((seg * hw + 31u) / 32u) + kScr;  // padded (pad_pair)
+            stride = packed_stride(hw, packp[m]);
             cap = G * packp[m];
         }
         cap = std::max(1u, std::min(cap, lds_budget / (stride * 4u)));
@@ -2897,10 +2912,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
         it.first = (uint32_t)order.size();
         it.count = (uint32_t)b.ms.size();
         it.wpm_log2 = (uint32_t)__builtin_ctz(b.wpm);
-        // packed books: 2 words per tick plus 4 words of padding per 32 ticks (pad_pair)
-        const uint32_t pticks = b.pipe == 3u ? (64u / b.share) * b.hw : 0u;
-        it.stride = b.pipe == 3u ? 2u * pticks + 4u * ((pticks + 31u) / 32u) + kScr
-                                 : 2u * 64u * b.tpl + 2u * b.hw + kScr;
+        it.stride = b.pipe == 3u ? packed_stride(b.hw, b.share) : 2u * 64u * b.tpl + 2u * b.hw + kScr;
         it.pipe = b.pipe;
         it.share = b.share;
         it.hoff = 2u * 64u * b.tpl;

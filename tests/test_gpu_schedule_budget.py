@@ -42,3 +42,13 @@ def test_overlap_needs_the_budget(Ks, budget, overlap):
     d = np.concatenate([E.markets(64, 600, K, 7) for K in Ks])
     t = _same_as_oracle(E, d, {"max_lds_bytes": budget})
     assert bool(t["overlap"].get(E.size_class(64, 600), 0)) == overlap
+
+
+# a wave of four packed books of 128 ticks takes 4864 bytes, of two 2432, a book by itself 1152; a
+# budget that holds no wave of packed books leaves the markets unpacked
+@pytest.mark.parametrize("budget,pack", [(4864, 4), (4863, 2), (2432, 2), (2431, 0), (1152, 0), (0, 4)])
+def test_packing_needs_the_budget(budget, pack):
+    E = _engine()
+    d = np.concatenate([E.markets(128, 16, 8, 7, M=4000), E.markets(20, 30, 2, 7, M=100)])
+    t = _same_as_oracle(E, d, {"max_lds_bytes": budget})
+    assert set(t["pack"].values()) == ({pack} if pack else set())
