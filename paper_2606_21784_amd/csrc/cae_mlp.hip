@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -26,7 +27,6 @@
 
 namespace {
 
-typedef short v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint16_t f2bf(float f)  // round to nearest even
@@ -812,17 +812,22 @@ __global__ void __launch_bounds__(256) adam_step(const AdamArgs a)
 
 // Inference of the whole network in one launch: a workgroup of 16 waves keeps its weights over
 // all of its tiles of rows.  A wave owns NT 16-column tiles of each hidden layer, over RT blocks
-// of 16 rows; narrow layers (H <= 128) split the waves over 2 or 4 groups of rows.  With RES
+// of 16 rows; narrow layers (H <= 128) split the waves over 2 to 16 groups of rows.  With RES
 // (H <= 256) the wave's W2 fragments stay in registers, otherwise they come from L2 for every
-// tile, whose RT = 4 blocks of rows share them.  The input of the next tile is fetched under the
-// current one, both hidden activations go through LDS, W3 sits in LDS as rows of 16 columns read
-// transposed; the output layer of 16 rows is one wave's chain, under the others' next tile.
+// tile, whose RT = 4 blocks of rows share them; both steps of W1 stay in registers (fetched again
+// for every tile, the second one of wide inputs made d_in = 40, H = 304, 65536 rows 103 us, 65
+// now).  SKIP: a wave does nothing for tiles of columns that a layer does not have; without it the
+// last tile's work is repeated (H = 272, 65536 rows: 106 us, 54 with it; H = 16, 300000 rows, all
+// waves on rows: 38 and 17).  The input of the next tile is fetched under the current one, both
+// hidden activations go through LDS, W3 sits in LDS as rows of 16 columns read transposed; the
+// output layer of 16 rows is one wave's chain, under the others' next tile.
 // Same rounding points and the same chains over k as mlp_layer and mlp_out, so the outputs equal
 // cae_mlp_forward's bit for bit.
 // H = 256: 6553 rows take 12.1 us, 65536 rows 39.6, one row 9.3 (32-row tiles on four waves that
-// streamed W2 from L2 for each: 21.5, 82.3 and 20.1); H = 496, 65536 rows: 134 (231).  A tile of 32
-// rows costs 2 us, of which the exponentials' instructions are 1.6; the set-up is instructions and
-// two memory latencies, about 7 us.
+// streamed W2 from L2 for each: 21.5, 82.3 and 20.1); H = 272, 65536 rows: 54 (70); H = 496: 110
+// (205); H = 16: 8.2 (8.1), 300000 rows 17 (25).  A tile of 32 rows costs 2 us, of which the
+// exponentials' instructions are 1.6; the set-up is instructions and two memory latencies, about
+// 7 us.
 constexpr uint32_t kPredMaxH = 496;
 constexpr uint32_t kPredWaves = 16, kPredThreads = 64 * kPredWaves;
 
@@ -835,7 +840,7 @@ struct PredArgs {
     const float *b1, *b2, *b3;
 };
 
-template <uint32_t NT, bool RES, uint32_t RT>
+template <uint32_t NT, bool RES, uint32_t RT, bool SKIP, uint32_t XN>
 __global__ void __launch_bounds__(kPredThreads) mlp_predict(const PredArgs a)
 {
     extern __shared__ __align__(16) uint16_t plds[];
@@ -844,8 +849,11 @@ __global__ void __launch_bounds__(kPredThreads) mlp_predict(const PredArgs a)
     const uint32_t r = lane & 15u, g = lane >> 4;
     const uint32_t H = a.H, Hp = (H + 31u) & ~31u, ldh = Hp + 8u, ct = H / 16u;
     const uint32_t Kx = (a.din + 31u) & ~31u, ldx = Kx + 8u;
-    const uint32_t wcols = 1u << a.cols_log2, wc = wave & (wcols - 1u), rg = wave >> a.cols_log2;
-    const uint32_t groups = kPredWaves >> a.cols_log2, rows = 16u * RT * groups;  // rows of a tile
+    const uint32_t wcols = 1u << a.cols_log2, groups = kPredWaves >> a.cols_log2;
+    // (with tiles missing, the waves of one column tile are consecutive: they lie on different SIMDs)
+    const uint32_t wc = SKIP ? wave / groups : wave & (wcols - 1u), rg = SKIP ? wave & (groups - 1u) : wave >> a.cols_log2;
+    const uint32_t rows = 16u * RT * groups;  // rows of a tile
+    const uint32_t mine = wc >= ct ? 0u : min((ct - wc + wcols - 1u) >> a.cols_log2, NT);  // the wave's tiles per layer
     // [rows][ldh] twice, the input [rows][ldx] twice, [Hp][16]
     uint16_t *h1 = plds, *h2 = h1 + rows * ldh, *xs = h2 + rows * ldh, *w3s = xs + 2u * rows * ldx;
     constexpr uint32_t K2 = 8;  // steps of 32 over H <= 256
@@ -854,7 +862,6 @@ __global__ void __launch_bounds__(kPredThreads) mlp_predict(const PredArgs a)
     // Every wave of the CU issues the set-up once (about 7 ns per instruction), so it is kept short:
     // 32-bit offsets from uniform bases, no division per element.
     // The input tile is contiguous: at most XN values per thread, thread tid + 1024 i.
-    constexpr uint32_t XN = 4u;
     const uint32_t xcount = rows * a.din;
     float xv[XN];
     uint32_t xo[XN];  // where they go in the LDS tile
@@ -899,9 +906,13 @@ __global__ void __launch_bounds__(kPredThreads) mlp_predict(const PredArgs a)
         for (uint32_t t = 0; t < 8u; ++t) e[t] = k + t < a.din ? e[t] : (uint16_t)0;
         return pack8(e);
     };
-    v8bf w1[NT];
+    v8bf w1[NT], w1b[NT];  // both steps of W1 (the second one of inputs wider than 32)
 #pragma unroll
     for (uint32_t j = 0; j < NT; ++j) w1[j] = load_w1(j, 0u);
+    if (Kx > 32u) {
+#pragma unroll
+        for (uint32_t j = 0; j < NT; ++j) w1b[j] = load_w1(j, 32u);
+    }
     const float b3 = a.b3[min(r, a.dout - 1u)];
     {
         const uint32_t k = tid >> 4, c = tid & 15u, off = 2u * (k * a.dout + min(c, a.dout - 1u));
@@ -937,83 +948,93 @@ __global__ void __launch_bounds__(kPredThreads) mlp_predict(const PredArgs a)
         const uint32_t row0 = rg * 16u * RT;  // the wave's rows of the tile
         uint16_t *xb = xs + buf * rows * ldx, *xn = xs + (buf ^ 1u) * rows * ldx;
         v4f acc[RT][NT];
-        // layer 1
+        // a hidden layer of the wave's first T tiles of columns
+        auto activate = [&](uint16_t *h, const float (&b)[NT], auto count) {
+            constexpr uint32_t T = decltype(count)::value;
 #pragma unroll
-        for (uint32_t q = 0; q < RT; ++q) {
-            const v8bf f = frag<16, false>(xb, ldx, row0 + 16u * q, 0u, lane);
-#pragma unroll
-            for (uint32_t j = 0; j < NT; ++j) acc[q][j] = Mfma<16>::mac(f, w1[j], v4f{0.f, 0.f, 0.f, 0.f});
-        }
-        if (Kx > 32u) {
-#pragma unroll
-            for (uint32_t j = 0; j < NT; ++j) {
-                const v8bf w = load_w1(j, 32u);
+            for (uint32_t j = 0; j < T; ++j) {
+                const uint32_t c = wc + wcols * j;
+                if (!SKIP && c >= ct) continue;
 #pragma unroll
                 for (uint32_t q = 0; q < RT; ++q)
-                    acc[q][j] = Mfma<16>::mac(frag<16, false>(xb, ldx, row0 + 16u * q, 32u, lane), w, acc[q][j]);
-            }
-        }
-        auto activate = [&](uint16_t *h, const float (&b)[NT]) {
 #pragma unroll
-            for (uint32_t j = 0; j < NT; ++j) {
-                const uint32_t c = wc + wcols * j;
-                if (c < ct) {
-#pragma unroll
-                    for (uint32_t q = 0; q < RT; ++q)
-#pragma unroll
-                        for (uint32_t t = 0; t < 4u; ++t)
-                            h[(row0 + 16u * q + 4u * g + t) * ldh + 16u * c + r] = f2bf_hw(silu(acc[q][j][t] + b[j]));
-                }
+                    for (uint32_t t = 0; t < 4u; ++t)
+                        h[(row0 + 16u * q + 4u * g + t) * ldh + 16u * c + r] = f2bf_hw(silu(acc[q][j][t] + b[j]));
             }
         };
-        activate(h1, b1);
+        auto layer1 = [&](auto count) {
+            constexpr uint32_t T = decltype(count)::value;
+#pragma unroll
+            for (uint32_t q = 0; q < RT; ++q) {
+                const v8bf f = frag<16, false>(xb, ldx, row0 + 16u * q, 0u, lane);
+#pragma unroll
+                for (uint32_t j = 0; j < T; ++j) acc[q][j] = Mfma<16>::mac(f, w1[j], v4f{0.f, 0.f, 0.f, 0.f});
+            }
+            if (Kx > 32u) {
+#pragma unroll
+                for (uint32_t j = 0; j < T; ++j) {
+#pragma unroll
+                    for (uint32_t q = 0; q < RT; ++q)
+                        acc[q][j] = Mfma<16>::mac(frag<16, false>(xb, ldx, row0 + 16u * q, 32u, lane), w1b[j], acc[q][j]);
+                }
+            }
+            activate(h1, b1, count);
+        };
+        auto layer2 = [&](auto count) {
+            constexpr uint32_t T = decltype(count)::value;
+#pragma unroll
+            for (uint32_t q = 0; q < RT; ++q)
+#pragma unroll
+                for (uint32_t j = 0; j < T; ++j) acc[q][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            if constexpr (RES) {
+#pragma unroll
+                for (uint32_t u = 0; u < K2; ++u)
+                    if (32u * u < H) {
+#pragma unroll
+                        for (uint32_t q = 0; q < RT; ++q) {
+                            const v8bf f = frag<16, false>(h1, ldh, row0 + 16u * q, 32u * u, lane);
+#pragma unroll
+                            for (uint32_t j = 0; j < T; ++j) acc[q][j] = Mfma<16>::mac(f, w2[j][u], acc[q][j]);
+                        }
+                    }
+            } else {
+                constexpr uint32_t KB = 2;  // steps whose weights are in flight together
+#pragma unroll 1
+                for (uint32_t k0 = 0; k0 < H; k0 += 32u * KB) {
+                    uint4 w[KB][T];
+#pragma unroll
+                    for (uint32_t u = 0; u < KB; ++u)
+#pragma unroll
+                        for (uint32_t j = 0; j < T; ++j) {
+                            const uint32_t n = min(16u * (wc + wcols * j), H - 16u) + r, k = k0 + 32u * u + 8u * g;
+                            w[u][j] = ld8u(a.W2T + (size_t)n * H + min(k, H - 8u));
+                        }
+#pragma unroll
+                    for (uint32_t u = 0; u < KB; ++u)
+                        if (k0 + 32u * u < H) {
+#pragma unroll
+                            for (uint32_t j = 0; j < T; ++j) w[u][j] = keep(k0 + 32u * u + 8u * g < H, w[u][j]);
+#pragma unroll
+                            for (uint32_t q = 0; q < RT; ++q) {
+                                const v8bf f = frag<16, false>(h1, ldh, row0 + 16u * q, k0 + 32u * u, lane);
+#pragma unroll
+                                for (uint32_t j = 0; j < T; ++j)
+                                    acc[q][j] = Mfma<16>::mac(f, __builtin_bit_cast(v8bf, w[u][j]), acc[q][j]);
+                            }
+                        }
+                }
+            }
+            activate(h2, b2, count);
+        };
+        auto of_mine = [&](auto layer) {  // no work for tiles that the layer does not have
+            if (!SKIP || (NT == 2u && mine == 2u)) layer(std::integral_constant<uint32_t, NT>{});
+            else if (mine != 0u) layer(std::integral_constant<uint32_t, 1>{});
+        };
+        of_mine(layer1);
         store_x(xn);
         load_x(min(tile + 2u * gridDim.x, tiles - 1u));
         __syncthreads();
-        // layer 2
-#pragma unroll
-        for (uint32_t q = 0; q < RT; ++q)
-#pragma unroll
-            for (uint32_t j = 0; j < NT; ++j) acc[q][j] = v4f{0.f, 0.f, 0.f, 0.f};
-        if constexpr (RES) {
-#pragma unroll
-            for (uint32_t u = 0; u < K2; ++u)
-                if (32u * u < H) {
-#pragma unroll
-                    for (uint32_t q = 0; q < RT; ++q) {
-                        const v8bf f = frag<16, false>(h1, ldh, row0 + 16u * q, 32u * u, lane);
-#pragma unroll
-                        for (uint32_t j = 0; j < NT; ++j) acc[q][j] = Mfma<16>::mac(f, w2[j][u], acc[q][j]);
-                    }
-                }
-        } else {
-            constexpr uint32_t KB = 2;  // steps whose weights are in flight together
-#pragma unroll 1
-            for (uint32_t k0 = 0; k0 < H; k0 += 32u * KB) {
-                uint4 w[KB][NT];
-#pragma unroll
-                for (uint32_t u = 0; u < KB; ++u)
-#pragma unroll
-                    for (uint32_t j = 0; j < NT; ++j) {
-                        const uint32_t n = min(16u * (wc + wcols * j), H - 16u) + r, k = k0 + 32u * u + 8u * g;
-                        w[u][j] = ld8u(a.W2T + (size_t)n * H + min(k, H - 8u));
-                    }
-#pragma unroll
-                for (uint32_t u = 0; u < KB; ++u)
-                    if (k0 + 32u * u < H) {
-#pragma unroll
-                        for (uint32_t j = 0; j < NT; ++j) w[u][j] = keep(k0 + 32u * u + 8u * g < H, w[u][j]);
-#pragma unroll
-                        for (uint32_t q = 0; q < RT; ++q) {
-                            const v8bf f = frag<16, false>(h1, ldh, row0 + 16u * q, k0 + 32u * u, lane);
-#pragma unroll
-                            for (uint32_t j = 0; j < NT; ++j)
-                                acc[q][j] = Mfma<16>::mac(f, __builtin_bit_cast(v8bf, w[u][j]), acc[q][j]);
-                        }
-                    }
-            }
-        }
-        activate(h2, b2);
+        of_mine(layer2);
         __syncthreads();
         // layer 3, 16 rows to a wave; it passes the next tile's first barrier before h2 is
         // written again
@@ -1552,6 +1573,22 @@ int scratch_of_current_device(void **out)
     return CAE_OK;
 }
 
+// Compute units of the current device, looked up once per device (a look-up is 0.25 us of a call).
+int cus_of_current_device(uint32_t *out)
+{
+    static std::atomic<uint32_t> known[kMaxDevices];
+    int dev = -1, n = 0;
+    hipError_t he = hipGetDevice(&dev);
+    const bool slot = he == hipSuccess && dev >= 0 && dev < kMaxDevices;
+    *out = slot ? known[dev].load(std::memory_order_relaxed) : 0u;
+    if (*out) return CAE_OK;
+    if (he == hipSuccess) he = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
+    if (he != hipSuccess || n < 1) return mfail(CAE_EHIP, hipGetErrorString(he));
+    *out = (uint32_t)n;
+    if (slot) known[dev].store(*out, std::memory_order_relaxed);
+    return CAE_OK;
+}
+
 // Argument checks shared by both training-step entry points (no device call).
 int check_train_args(const cae_mlp *net, const float *x, const float *target, const float *m, const float *v,
                      uint32_t N, uint32_t step, int loss_kind, float delta, const float *loss)
@@ -1681,31 +1718,43 @@ int cae_mlp_predict(const cae_mlp *net, const float *x, float *y, uint32_t N, vo
     a.b1 = net->params + l.b1;
     a.b2 = net->params + l.b2;
     a.b3 = net->params + l.b3;
-    int dev = 0, cus = 0;
-    hipError_t he = hipGetDevice(&dev);
-    if (he == hipSuccess) he = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (he != hipSuccess) return mfail(CAE_EHIP, hipGetErrorString(he));
+    uint32_t cus = 0;
+    rc = cus_of_current_device(&cus);
+    if (rc) return rc;
     a.cols_log2 = H > 128u ? 4u : (H > 64u ? 3u : 2u);
-    const uint32_t groups = kPredWaves >> a.cols_log2;
     const uint64_t Hp = (H + 31u) & ~31u, Kx = (din + 31u) & ~31u;
-    // blocks of 16 rows per wave: more rows share each pass over the weights, once every CU has a
-    // tile of them; the tile's input is at most four values per thread
     const auto lds_bytes = [&](uint64_t rows) { return 2u * (2u * rows * (Hp + 8u) + 2u * rows * (Kx + 8u) + Hp * 16u); };
+    // waves without a tile of columns skip its work where that leaves every SIMD less of it (beyond
+    // 448 columns some SIMD's four waves all have two tiles: H = 464, 65536 rows 105 us either way)
+    const auto skips = [&](uint32_t cols_log2) { return H <= 256u ? H < 16u << cols_log2 : H <= 448u; };
+    // more rows share each pass over the weights, once every CU has a tile of them and as long as
+    // the tile's input fits its threads' registers: first the waves that a narrow layer has no
+    // columns for take rows, then blocks of 16 rows per wave.  Eight input values per thread instead
+    // of four pay where the waves are few (d_in = 40, 300000 rows: H = 16 36 us to 27, H = 48 46 to
+    // 41) and cost registers elsewhere (H = 208 148 to 154)
+    const auto may_double = [&](uint32_t rows, uint32_t cols_log2) {
+        const uint32_t inputs = H <= 48u && skips(cols_log2) ? 8u : 4u;
+        return (uint64_t)rows * cus < N && 2u * rows * din <= inputs * kPredThreads && lds_bytes(2u * rows) <= 160u * 1024u;
+    };
+    while (a.cols_log2 > 0u && H <= 8u << a.cols_log2 && may_double(16u * (kPredWaves >> a.cols_log2), a.cols_log2 - 1u))
+        --a.cols_log2;
+    const uint32_t groups = kPredWaves >> a.cols_log2, most = H > 256u ? 4u : std::min(2u, kPredWaves / groups);
     uint32_t rt = 1;
-    const uint32_t most = H > 256u ? 4u : 2u;
-    while (2u * rt <= most && (uint64_t)16u * rt * groups * (uint32_t)cus < N &&
-           32u * rt * groups * din <= 4u * kPredThreads && lds_bytes(32u * rt * groups) <= 160u * 1024u)
-        rt *= 2u;
+    while (2u * rt <= most && may_double(16u * rt * groups, a.cols_log2)) rt *= 2u;
     const uint32_t rows = 16u * rt * groups;
     const size_t lds = lds_bytes(rows);
     const uint32_t tiles = (uint32_t)(((uint64_t)N + rows - 1u) / rows);
-    const dim3 grid(std::min(tiles, (uint32_t)cus)), block(kPredThreads);
+    const bool skip = skips(a.cols_log2);
+    const dim3 grid(std::min(tiles, cus)), block(kPredThreads);
     const hipStream_t s = (hipStream_t)stream;
-    if (H <= 256u && rt == 1u) hipLaunchKernelGGL((mlp_predict<1, true, 1>), grid, block, lds, s, a);
-    else if (H <= 256u) hipLaunchKernelGGL((mlp_predict<1, true, 2>), grid, block, lds, s, a);
-    else if (rt == 1u) hipLaunchKernelGGL((mlp_predict<2, false, 1>), grid, block, lds, s, a);
-    else if (rt == 2u) hipLaunchKernelGGL((mlp_predict<2, false, 2>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((mlp_predict<2, false, 4>), grid, block, lds, s, a);
+    const auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, s, a); };
+    const auto either = [&](auto whole, auto some) { launch(skip ? some : whole); };
+    if (rows * din > 4u * kPredThreads) launch(rt == 1u ? mlp_predict<1, true, 1, true, 8> : mlp_predict<1, true, 2, true, 8>);
+    else if (H <= 256u && rt == 1u) either(mlp_predict<1, true, 1, false, 4>, mlp_predict<1, true, 1, true, 4>);
+    else if (H <= 256u) either(mlp_predict<1, true, 2, false, 4>, mlp_predict<1, true, 2, true, 4>);
+    else if (rt == 1u) either(mlp_predict<2, false, 1, false, 4>, mlp_predict<2, false, 1, true, 4>);
+    else if (rt == 2u) either(mlp_predict<2, false, 2, false, 4>, mlp_predict<2, false, 2, true, 4>);
+    else either(mlp_predict<2, false, 4, false, 4>, mlp_predict<2, false, 4, true, 4>);
     return launch_status();
 }
 
