@@ -183,9 +183,9 @@ struct LayerArgs {
     uint16_t *O;         // M x N
 };
 
-// One layer product of the hidden width, C = A B with a fused epilogue: four waves per workgroup
-// in a 2 x 2 arrangement of WM x WN output tiles each, operands staged through LDS in blocks of 64
-// of the reduction, the next block's global loads in flight during the current block's products.
+// One layer product of the hidden width, C = A B with a fused epilogue: four waves per workgroup,
+// WC of them side by side, with WM x WN output tiles each, operands staged through LDS in blocks of
+// 64 of the reduction, the next block's global loads in flight during the current block's products.
 //   AF32: A is fp32 and short (the input, or the output gradient): one block.
 //   KMAJOR: B is read k-major through transposing LDS reads (W1, W2 forward); otherwise its rows
 //   are the reduction (W2 backward), or short rows of any length (W3 backward, AF32).
@@ -194,11 +194,12 @@ struct LayerArgs {
 // with two-byte operand loads: 475 and 882 us), of which the products are about half (matrix cores
 // busy 8.4e6 of 1.9e7 SIMD cycles); the other half is the exponentials and the stores of the
 // epilogue, which the short products (12 and 9 us, from 35 and 20) consist of.
-template <int WM, int WN, bool AF32, bool KMAJOR, int EPI>
+template <int WM, int WN, uint32_t WC, bool AF32, bool KMAJOR, int EPI>
 __global__ void __launch_bounds__(256) mlp_layer(const LayerArgs g)
 {
     constexpr int MF = WM >= 32 ? 32 : 16;
-    constexpr uint32_t MI = WM / MF, NI = WN / MF, BM = 2 * WM, BN = 2 * WN;
+    constexpr uint32_t MI = WM / MF, NI = WN / MF, BM = 4u / WC * WM, TN = WC * WN;
+    constexpr uint32_t BN = TN < 32u ? 32u : TN;  // columns brought to LDS for the tile's TN
     using MM = Mfma<MF>;
     constexpr uint32_t kBufs = AF32 ? 1u : 2u;
     constexpr uint32_t kLdB = KMAJOR ? BN + kPadK : kLdR;
@@ -206,10 +207,10 @@ __global__ void __launch_bounds__(256) mlp_layer(const LayerArgs g)
     __shared__ __align__(16) uint16_t sA[kBufs * BM * kLdR];
     __shared__ __align__(16) uint16_t sB[kBufs * kTileB];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint32_t wm = wave >> 1, wn = wave & 1u;
-    const uint32_t tn = (g.N + BN - 1u) / BN;
+    const uint32_t wm = wave / WC, wn = wave % WC;
+    const uint32_t tn = (g.N + TN - 1u) / TN;
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const uint32_t row0 = tile / tn * BM, col0 = tile % tn * BN;
+    const uint32_t row0 = tile / tn * BM, col0 = tile % tn * TN;
 
     // 16-byte chunks of each operand block per thread, at 32-bit offsets from the block's uniform
     // base.  Every load is issued without a condition: rows and columns past the end are clamped
@@ -396,31 +397,34 @@ __global__ void __launch_bounds__(256) mlp_layer(const LayerArgs g)
             }
         }
     };
-    if (row0 + BM <= g.M && col0 + BN <= g.N) finish(std::true_type{});
+    if (row0 + BM <= g.M && col0 + TN <= g.N) finish(std::true_type{});
     else finish(std::false_type{});
 }
 
-// Output layer y = h W3 + b3: 16 rows per workgroup.  All four waves bring the rows and W3 (rows
-// of 16 columns, read transposed) into LDS, one wave runs the chain over H.
+// Output layer y = h W3 + b3: NB blocks of 16 rows per workgroup.  All four waves bring the rows and
+// W3 (rows of 16 columns, read transposed) into LDS, one wave per block runs the chain over H.  At
+// H = 16 the chain is one step and the workgroups' fixed costs are the time: 65536 rows take 6.4 us
+// with one block, 4.6 with four (wider layers gain less or lose).
+template <uint32_t NB>
 __global__ void __launch_bounds__(256) mlp_out(const uint16_t *h, const uint16_t *W3, const float *b3, float *y,
                                                uint32_t M, uint32_t H, uint32_t dout)
 {
     extern __shared__ __align__(16) uint16_t olds[];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, r = lane & 15u, gq = lane >> 4;
     const uint32_t Hp = (H + 31u) & ~31u, ldh = Hp + 8u;
-    uint16_t *hs = olds, *w3s = olds + 16u * ldh;  // [16][ldh], [Hp][16]
-    const uint32_t row0 = blockIdx.x * 16u, hc = Hp / 8u;
-    for (uint32_t e0 = tid; e0 < 16u * hc; e0 += 2048u) {
+    uint16_t *hs = olds, *w3s = olds + 16u * NB * ldh;  // [16 NB][ldh], [Hp][16]
+    const uint32_t row0 = blockIdx.x * 16u * NB, hc = Hp / 8u;
+    for (uint32_t e0 = tid; e0 < 16u * NB * hc; e0 += 2048u) {
         uint4 v[8];
 #pragma unroll
         for (uint32_t c = 0; c < 8u; ++c) {
             const uint32_t e = e0 + 256u * c, rr = e / hc, k = 8u * (e % hc);
-            v[c] = ld8u(h + (size_t)min(row0 + min(rr, 15u), M - 1u) * H + min(k, H - 8u));
+            v[c] = ld8u(h + (size_t)min(row0 + min(rr, 16u * NB - 1u), M - 1u) * H + min(k, H - 8u));
         }
 #pragma unroll
         for (uint32_t c = 0; c < 8u; ++c) {
             const uint32_t e = e0 + 256u * c;
-            if (e < 16u * hc) *reinterpret_cast<uint4 *>(hs + e / hc * ldh + 8u * (e % hc)) = keep(8u * (e % hc) < H, v[c]);
+            if (e < 16u * NB * hc) *reinterpret_cast<uint4 *>(hs + e / hc * ldh + 8u * (e % hc)) = keep(8u * (e % hc) < H, v[c]);
         }
     }
     if (dout == 16u) {
@@ -433,14 +437,15 @@ __global__ void __launch_bounds__(256) mlp_out(const uint16_t *h, const uint16_t
         }
     }
     __syncthreads();
-    if (tid >= 64u) return;
+    if (tid >= 64u * NB) return;
+    const uint32_t at = 16u * (tid >> 6), wrow = row0 + at;  // the wave's rows
     v4f acc = {0.f, 0.f, 0.f, 0.f};
     for (uint32_t k0 = 0; k0 < Hp; k0 += 32u)
-        acc = Mfma<16>::mac(frag<16, false>(hs, ldh, 0u, k0, lane), frag<16, true>(w3s, 16u, 0u, k0, lane), acc);
+        acc = Mfma<16>::mac(frag<16, false>(hs, ldh, at, k0, lane), frag<16, true>(w3s, 16u, 0u, k0, lane), acc);
     if (r < dout) {
 #pragma unroll
         for (uint32_t t = 0; t < 4u; ++t)
-            if (row0 + 4u * gq + t < M) y[(size_t)(row0 + 4u * gq + t) * dout + r] = acc[t] + b3[r];
+            if (wrow + 4u * gq + t < M) y[(size_t)(wrow + 4u * gq + t) * dout + r] = acc[t] + b3[r];
     }
 }
 
@@ -1845,21 +1850,28 @@ constexpr uint32_t kLayerBlocks = 256;  // workgroups that fill the chip
 // Launches one layer product in the widest workgroup tile that gives every CU a workgroup: at
 // 4096 x 1024 x 1024 tiles of 128 x 64 take 21.5 us, 64 x 64 22.4, 128 x 128 (one workgroup of four
 // waves per CU) 22.9.  Short products spend their time in the epilogue and take 64 x 64 at most.
+// Layers of 16 and 32 columns leave wider tiles mostly empty: 65536 rows of H = 16 take 13.4 us
+// (second layer) in 128 x 64, 7.9 in 32 x 32 and 5.8 with the four waves below each other, 64 x 16;
+// the forward pass of H = 32 28.9 us with tiles of 64 columns, 22.8 of 32.
 template <bool AF32, bool KMAJOR, int EPI>
 void layer(const LayerArgs &g, hipStream_t s)
 {
     auto blocks = [&](uint32_t bm, uint32_t bn) { return ((g.M + bm - 1u) / bm) * ((g.N + bn - 1u) / bn); };
     const dim3 block(256);
+    if (g.N == 16u && blocks(64u, 16u) >= kLayerBlocks) {
+        hipLaunchKernelGGL((mlp_layer<16, 16, 1, AF32, KMAJOR, EPI>), dim3(blocks(64u, 16u)), block, 0, s, g);
+        return;
+    }
     if constexpr (!AF32) {
-        if (blocks(128u, 64u) >= kLayerBlocks) {
-            hipLaunchKernelGGL((mlp_layer<64, 32, AF32, KMAJOR, EPI>), dim3(blocks(128u, 64u)), block, 0, s, g);
+        if (g.N > 32u && blocks(128u, 64u) >= kLayerBlocks) {
+            hipLaunchKernelGGL((mlp_layer<64, 32, 2, AF32, KMAJOR, EPI>), dim3(blocks(128u, 64u)), block, 0, s, g);
             return;
         }
     }
-    if (blocks(64u, 64u) >= kLayerBlocks)
-        hipLaunchKernelGGL((mlp_layer<32, 32, AF32, KMAJOR, EPI>), dim3(blocks(64u, 64u)), block, 0, s, g);
+    if (g.N > 32u && blocks(64u, 64u) >= kLayerBlocks)
+        hipLaunchKernelGGL((mlp_layer<32, 32, 2, AF32, KMAJOR, EPI>), dim3(blocks(64u, 64u)), block, 0, s, g);
     else
-        hipLaunchKernelGGL((mlp_layer<16, 16, AF32, KMAJOR, EPI>), dim3(blocks(32u, 32u)), block, 0, s, g);
+        hipLaunchKernelGGL((mlp_layer<16, 16, 2, AF32, KMAJOR, EPI>), dim3(blocks(32u, 32u)), block, 0, s, g);
 }
 
 // The layer-by-layer forward pass: activations and pre-activations are kept in ws for
@@ -1890,8 +1902,13 @@ int forward_impl(const cae_mlp *net, const float *x, float *y, uint32_t N, void 
     g.Z = reinterpret_cast<float *>(b + w.z2);
     g.O = reinterpret_cast<uint16_t *>(b + w.h2);
     layer<false, true, EPI_HIDDEN>(g, s);
-    const size_t Hp = (H + 31u) & ~31u, lds = 2u * (16u * (Hp + 8u) + 16u * Hp);
-    hipLaunchKernelGGL(mlp_out, dim3((N + 15u) / 16u), dim3(256), lds, s, g.O, W3, net->params + l.b3, y, N, H, dout);
+    const size_t Hp = (H + 31u) & ~31u;
+    const auto out = [&](auto kernel, uint32_t rows) {
+        hipLaunchKernelGGL(kernel, dim3((N + rows - 1u) / rows), dim3(256), 2u * (rows * (Hp + 8u) + 16u * Hp), s, g.O, W3,
+                           net->params + l.b3, y, N, H, dout);
+    };
+    if (H == 16u && N >= 64u * kLayerBlocks) out(mlp_out<4>, 64u);
+    else out(mlp_out<1>, 16u);
     return launch_status();
 }
 
