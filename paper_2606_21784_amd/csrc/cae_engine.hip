@@ -2268,14 +2268,14 @@ __global__ void __launch_bounds__(64) cae_naive_kernel(const EngineArgs args, ui
 }
 
 // One clearing pass over n books of L ticks, the books in registers from memory to memory.  Books
-// of up to 128 ticks run four to a wave, a row of 16 lanes each, TPL consecutive ticks per lane;
-// larger ones one to a wave, in CH chunks of 256 ticks of which each lane holds four consecutive
-// ones, so that every access is 16 bytes per lane over consecutive addresses (the hardware takes
-// them at any word address), except in the one lane that holds fewer ticks, which goes tick by
-// tick.  By the definitions: V* = max min(D, S), the clearing tick is the number of ticks with
-// S < V* (S rises with the tick), the residuals are differences of unmatched quantities (see
-// unmatched).  Bound by memory, 16 bytes per tick and book: 16384 books of 256 ticks take 9.7 us
-// (6.9 TB/s, out of the last-level cache), 800000 of 5 ticks 27.8 (one wave per book: 103).
+// of up to 128 ticks run four to a wave, a row of 16 lanes each; larger ones one to a wave.  A book
+// is cut in CH chunks of T consecutive ticks per lane (64 T ticks, on rows 16 T), so that every
+// access is 4 T bytes per lane over consecutive addresses (the hardware takes them at any word
+// address), except in the one lane that holds fewer ticks, which goes tick by tick.  By the
+// definitions: V* = max min(D, S), the clearing tick is the number of ticks with S < V* (S rises
+// with the tick), the residuals are differences of unmatched quantities (see unmatched).  Bound by
+// memory, 16 bytes per tick and book: 16384 books of 256 ticks take 9.7 us (6.9 TB/s, out of the
+// last-level cache), 800000 of 5 ticks 27.8 (one wave per book: 103).
 typedef uint32_t v4u_any __attribute__((ext_vector_type(4), aligned(4), may_alias));
 typedef uint32_t v2u_any __attribute__((ext_vector_type(2), aligned(4), may_alias));
 
@@ -2337,7 +2337,7 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x)
     return readlane(x, 63);
 }
 
-// ROW: a row of 16 lanes per book (CH = 1); otherwise the wave's book, T = 4 ticks per chunk.
+// ROW: a row of 16 lanes per book; otherwise the wave's book.
 template <int CH, int T, bool ROW>
 __global__ void __launch_bounds__(256) cae_clear_kernel(uint32_t L, uint32_t n, uint32_t *book,
                                                         uint32_t *pstar, uint32_t *vstar)
@@ -2373,7 +2373,7 @@ __global__ void __launch_bounds__(256) cae_clear_kernel(uint32_t L, uint32_t n, 
         eb[c] = Tb + ib - sb;
         ea[c] = Ta + ia - sa;
         Tb += ROW ? row_last(ib) : readlane(ib, 63);
-        if constexpr (CH > 1) Ta += readlane(ia, 63);
+        if constexpr (CH > 1) Ta += ROW ? row_last(ia) : readlane(ia, 63);
     }
     uint32_t mv = 0;
 #pragma unroll
@@ -3244,7 +3244,21 @@ int cae_clear(uint32_t L, uint32_t M, uint32_t *dev_book, uint32_t *dev_pstar, u
     if (L <= 16u) launch(cae_clear_kernel<1, 1, true>, 16u);
     else if (L <= 32u) launch(cae_clear_kernel<1, 2, true>, 16u);
     else if (L <= 64u) launch(cae_clear_kernel<1, 4, true>, 16u);
-    else if (L <= 128u) launch(cae_clear_kernel<1, 8, true>, 16u);
+    else if (L <= 128u) {
+        // on a row of lanes: 16-byte accesses while the books fit the L2s, 8-byte ones while they fit
+        // the last-level cache, where more and shorter accesses keep it busier; out of HBM 16-byte
+        // ones again, except that longer rows off a multiple of 16 bytes put too many of them across
+        // lines, and a wave takes a book with 4 bytes per lane.  us for one wave per book through
+        // LDS / 32 bytes per lane on rows / as here: L = 127: 8 MB 4.9 / 5.3 / 4.5, 33 MB 12.4 /
+        // 13.4 / 10.7, 67 MB 22.5 / 24.1 / 21.2, 268 MB 89.9 / 106.8 / 89.2; L = 124: 4.4 / 5.1 /
+        // 4.2, 11.3 / 12.3 / 9.9, 21.5 / 23.2 / 20.7, 88.5 / 96.0 / 79.5; L = 65, 67 MB 29.8 / 27.5 /
+        // 26.3; L = 128 gains least: 560 MB 203 / - / 212
+        const uint64_t bytes = 8ull * L * M;
+        const bool cached = bytes <= 250000000ull;
+        if (bytes <= 16ull << 20 || (!cached && (L % 4u == 0u || L < 84u))) launch(cae_clear_kernel<2, 4, true>, 16u);
+        else if (cached) launch(cae_clear_kernel<4, 2, true>, 16u);
+        else launch(cae_clear_kernel<2, 1, false>, 4u);
+    }
     else if (L <= 256u) launch(cae_clear_kernel<1, 4, false>, 4u);
     else if (L <= 512u) launch(cae_clear_kernel<2, 4, false>, 4u);
     else launch(cae_clear_kernel<4, 4, false>, 4u);
