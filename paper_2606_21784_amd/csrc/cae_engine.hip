@@ -3243,7 +3243,15 @@ int cae_clear(uint32_t L, uint32_t M, uint32_t *dev_book, uint32_t *dev_pstar, u
     };
     if (L <= 16u) launch(cae_clear_kernel<1, 1, true>, 16u);
     else if (L <= 32u) launch(cae_clear_kernel<1, 2, true>, 16u);
-    else if (L <= 64u) launch(cae_clear_kernel<1, 4, true>, 16u);
+    else if (L <= 64u) {
+        const bool odd = L % 4u == 3u || (L % 4u == 1u && L < 48u);
+        // where a book ends in a lane of two or three single ticks, pairs of them per lane: L = 62, 130
+        // MB of books 39.2 us in fours, 38.1 in pairs; odd ones out of HBM only (L = 63, 280 MB: 125.5
+        // / 108.8; 130 MB: 38.6 / 41.4), of one single tick the short ones (L = 33, 560 MB: 273.9 /
+        // 243.2, L = 61: 236 / 241).  One wave per book through LDS: 40.3, 126.8, 447, 265
+        if (L % 4u == 2u || (odd && 8ull * L * M > 250000000ull)) launch(cae_clear_kernel<2, 2, true>, 16u);
+        else launch(cae_clear_kernel<1, 4, true>, 16u);
+    }
     else if (L <= 128u) {
         // on a row of lanes: 16-byte accesses while the books fit the L2s, 8-byte ones while they fit
         // the last-level cache, where more and shorter accesses keep it busier; out of HBM 16-byte
@@ -3252,10 +3260,13 @@ int cae_clear(uint32_t L, uint32_t M, uint32_t *dev_book, uint32_t *dev_pstar, u
         // LDS / 32 bytes per lane on rows / as here: L = 127: 8 MB 4.9 / 5.3 / 4.5, 33 MB 12.4 /
         // 13.4 / 10.7, 67 MB 22.5 / 24.1 / 21.2, 268 MB 89.9 / 106.8 / 89.2; L = 124: 4.4 / 5.1 /
         // 4.2, 11.3 / 12.3 / 9.9, 21.5 / 23.2 / 20.7, 88.5 / 96.0 / 79.5; L = 65, 67 MB 29.8 / 27.5 /
-        // 26.3; L = 128 gains least: 560 MB 203 / - / 212
+        // 26.3.  From 120 ticks on the rows gain nothing out of HBM, and 8-byte accesses of a wave per
+        // book are faster there: L = 128, 560 MB 202 / - / 212 on rows, 190 so (L = 124 217, 221, 214;
+        // 270 MB of L = 128: 90, 72, 79)
         const uint64_t bytes = 8ull * L * M;
         const bool cached = bytes <= 250000000ull;
-        if (bytes <= 16ull << 20 || (!cached && (L % 4u == 0u || L < 84u))) launch(cae_clear_kernel<2, 4, true>, 16u);
+        if (bytes > 350000000ull && L % 4u == 0u && L > 120u) launch(cae_clear_kernel<1, 2, false>, 4u);
+        else if (bytes <= 16ull << 20 || (!cached && (L % 4u == 0u || L < 84u))) launch(cae_clear_kernel<2, 4, true>, 16u);
         else if (cached) launch(cae_clear_kernel<4, 2, true>, 16u);
         else launch(cae_clear_kernel<2, 1, false>, 4u);
     }
