@@ -2608,9 +2608,10 @@ struct AutoClass {
 
 // Schedule of a size class whose waves the caller leaves to the library: tpl ticks per lane, A
 // agents (the class's mean), `full` waves that would spread the chip's 16 waves per CU over the
-// ensemble in proportion to cost (4096 / M for M equal markets on 256 CUs), plain: some market of
-// the class uses SplitMix64, or the mid-price model with more bins than a flush places in one pass
-// (the overlapped schedule does not pay for those); mid: some market uses the mid-price model.
+// ensemble in proportion to cost (4096 / M for M equal markets on 256 CUs), noise: NOISE agents'
+// share of the class's agents, plain: some market of the class uses SplitMix64, or the mid-price
+// model with more bins than a flush places in one pass (those run in lock step); mid: some market
+// uses the mid-price model.
 //   * A market gets its share of the waves, as long as every wave has work: a row of 64 agents
 //     each when the chip is nearly empty (full >= 16), two rows otherwise; few agents or a book
 //     longer than the order flow fill one wave (the clearing is one wave's work whatever the
@@ -2624,28 +2625,69 @@ struct AutoClass {
 //     four rows has use for a wave per row on a fuller chip too (L = 128, A = 256, M = 960: four
 //     waves 1.08, two 1.14, one 1.32; L = 64, A = 128, M = 960: two 0.83, one 0.96), and none for
 //     more than 8 below A = 2048 (L = 256, A = 1024, M = 256: 16 waves 1.09, 8 1.00); beyond
-//     M = 1600 the small ones keep one wave (L = 256, A = 128, M = 2048: two 1.43, one 1.23).
+//     M = 1575 the small ones keep one wave (L = 256, A = 128, M = 2048: two 1.43, one 1.23; L = 16,
+//     A = 256, M = 1600: two 1.57, one 1.22).  Not for mid-price markets of mostly NOISE agents with
+//     eight rows per wave: a row of marketable and other orders costs more in the bins than in the
+//     book (L = 64, A = 16384, M = 100: 7.1 with, 6.0 without).
 //     The clearing wave's share of the rows is what its clearing leaves of an even one.
-// Over 300 shapes (L 64..1024, A 16..16384, M 4..8192) the rule is within 1.1 % of the best of the
-// schedules it chooses from, in geometric mean (17 % at most); a rule on A alone lost 15 %.
-AutoClass auto_class(uint32_t tpl, double A, double full, bool plain, bool mid)
+//   * In lock step three rows take four waves on a nearly empty chip (SplitMix64, L = 512, A = 192,
+//     M = 64: two 1.85, one 1.53, four 1.47), and many SplitMix64 markets one wave (L = 512, A = 512,
+//     M = 1600: two 2.74, one 2.43).
+//   * Large markets (32 rows or more) whose workgroups would leave the fullest CU with 15 % more than
+//     the mean take larger groups, of one market each.  L = 256, us per step for the share's power
+//     of two / this: A = 4096, M = 1200 7.7 / 6.2 (two waves, four), A = 16384, M = 600 14.5 / 13.1
+//     (four, eight), A = 2048, M = 2100 7.9 / 6.1 (one, four).  Eight waves only while that leaves at
+//     most three markets to a CU (A = 4096, M = 800, mid-price: 6.2 with four, 6.9 with eight), four
+//     with two rows per wave and tick of a longer book (A = 2048, L = 512, M = 1200, last-tick:
+//     overlapped 4.5, in lock step 4.3), and one wave beyond 2400 books of more than 256 ticks (A =
+//     2048, L = 512, M = 2600: one 8.7, four 9.1).
+// Over 1563 shapes (L 16..1024, A 130..16384, M 1..4200, both models and generators) the rule is 16 %
+// faster in geometric mean than a rule on A alone (one wave per 512 agents, no overlap, no packing),
+// and slower than it by more than 2 % on 18 of them: 7 % for SplitMix64 markets of L = 512, A = 1000,
+// M = 800..900, at most 4 % elsewhere (SplitMix64 of A = 700 and 1500, mid-price ones of A = 512).
+AutoClass auto_class(uint32_t tpl, double A, double full, double noise, bool plain, bool mid)
 {
     const uint32_t rows = (uint32_t)std::ceil(A / 64.0);
     AutoClass c{1u, 0u};
+    const bool splitmix = plain && !mid;
     mid = mid && !plain;
     if (A <= (mid ? 64.0 : 128.0)) return c;
     double cap;
     if (full >= 16.0) {
         cap = rows <= 4u || (!plain && (tpl <= 4u || A >= 2048.0)) ? rows : rows / 2.0;
+        if (rows == 3u && (plain || (tpl >= 8u && !mid))) cap = 4.0;
         if (mid && A < 2048.0) cap = std::min(cap, 8.0);
     } else {
-        cap = plain ? rows / 4.0 : !mid || rows > 4u ? rows / 2.0 : full >= 2.5 ? rows : 1.0;
-        if (tpl >= 8u && !mid) cap = std::min(cap, A / (32.0 * tpl));
+        cap = !mid || rows > 4u ? rows / 2.0 : full >= 2.6 ? rows : 1.0;
+        if (plain) cap = rows <= 16u && full < 2.6 ? 1.0 : rows / 4.0;
+        if (tpl >= 8u && !mid) cap = std::min(cap, A / ((plain && tpl == 8u && full >= 5.5 ? 24.0 : 32.0) * tpl));
     }
     const double w = std::min({full, cap, 16.0});
     while (2.0 * c.wpm <= w) c.wpm <<= 1;
-    if (c.wpm < 2u || plain || (tpl >= 8u && !mid && full >= 16.0 && A < 2048.0)) return c;
+    bool lockstep = plain;
+    if (full < 16.0 && c.wpm <= 4u && rows > 16u) {
+        const double mean = 16.0 / full, per = std::max(4u, c.wpm) / c.wpm;  // markets per CU and per workgroup
+        const bool uneven = per * std::ceil(mean / per - 1e-6) > 1.15 * mean;
+        const bool room = plain || tpl < 8u || rows / (2u * c.wpm) >= 2u * tpl;
+        if (uneven && rows < 32u) {
+            if (splitmix && c.wpm == 1u && full >= 1.7) c.wpm = 2u;
+        } else if (uneven && c.wpm == 1u) {
+            if (tpl < 8u || (tpl == 8u && full >= 1.7)) c.wpm = 4u;
+        } else if (uneven && c.wpm == 2u) {
+            const bool more = rows >= 64u ? room && tpl <= 8u
+                              : plain     ? tpl <= 8u || (splitmix && full >= 3.2)
+                                          : tpl >= 4u && tpl <= 8u && full >= 3.2;
+            if (more) {
+                lockstep = lockstep || rows < 64u;
+                c.wpm = 4u;
+            }
+        } else if (uneven && rows >= 64u && room && tpl <= 8u && mean < 2.7) {
+            c.wpm = 8u;
+        }
+    }
+    if (c.wpm < 2u || lockstep || (tpl >= 8u && !mid && full >= 16.0 && A < 2048.0)) return c;
     const uint32_t even = rows / c.wpm;
+    if (mid && even >= 8u && noise >= 0.75) return c;
     uint32_t share = 0;
     if (tpl >= 16u || (tpl == 8u && ((A < 2048.0 && !(mid && even >= 8u)) || full >= 8.0))) share = 0;
     else if (even >= 8u) share = 3u * even / 4u;
@@ -2738,7 +2780,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     // from its share of the ensemble's cost
     bool auto_c[CAE_NUM_CLASSES] = {};
     {
-        double cost[CAE_NUM_CLASSES] = {}, agents[CAE_NUM_CLASSES] = {}, total = 0.0, dearest = 0.0;
+        double cost[CAE_NUM_CLASSES] = {}, agents[CAE_NUM_CLASSES] = {}, noise[CAE_NUM_CLASSES] = {}, total = 0.0, dearest = 0.0;
         uint32_t count[CAE_NUM_CLASSES] = {}, need[CAE_NUM_CLASSES] = {}, bins[CAE_NUM_CLASSES] = {}, A_max = 0;
         bool plain[CAE_NUM_CLASSES] = {}, mid[CAE_NUM_CLASSES] = {}, all_auto = true, small_last = maxL <= kPackMaxL;
         for (uint32_t m = 0; m < M; ++m) {
@@ -2748,6 +2790,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             count[c] += 1;
             cost[c] += w;
             agents[c] += d.A;
+            noise[c] += d.n_noise;
             total += w;
             plain[c] |= ((d.flags >> CAE_GEN_SHIFT) & 0xFFu) != CAE_GEN_PHILOX ||
                         ((d.flags & CAE_MODEL_MASK) == CAE_MODEL_MID && d.K > kMidOnePassK);
@@ -2777,7 +2820,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             const double A = agents[c] / count[c];
             AutoClass a = dearest > 1.5 * total / M
                               ? auto_class_mixed(A, full, 16.0 * ncu * dearest / total, plain[c])
-                              : auto_class(1u << (c / 8u), A, full, plain[c], mid[c]);
+                              : auto_class(1u << (c / 8u), A, full, noise[c] / agents[c], plain[c], mid[c]);
             // a caller's group size below what the class's markets need is refused further down
             if (t.waves_per_group && need[c] > t.waves_per_group) a.wpm = need[c];
             while (t.waves_per_group && need[c] <= t.waves_per_group && a.wpm > t.waves_per_group) a.wpm >>= 1;
