@@ -2932,6 +2932,28 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             for (uint32_t mm : b.ms) c = std::max(c, cost[mm]);
             done.push_back({c, b});
         }
+    // Fewer items than CUs: the fullest ones are halved, those of more than four waves until every CU
+    // has an item, the others (a wave or less per SIMD) until every fourth one has.  The group size
+    // follows the largest markets, so the small ones of a mixture would share a few CUs at 16 waves
+    // each (a tenth A = 4096, the rest A = 256, L = 1024, M = 256, us per step: 5.6, spread out 3.6);
+    // L = 256, A = 300, M = 32 SplitMix64 ones of one wave: 1.68 in fours, 1.58 alone.  Beyond 64 items the
+    // markets of one CU do not hold each other up (M = 256 on one wave: 1 to 3 % slower alone).
+    while (done.size() < ncu) {
+        size_t most = done.size();
+        for (size_t i = 0; i < done.size(); ++i) {
+            const Bin &b = done[i].second;
+            const bool splits = (b.pipe == 0u || b.pipe == 2u) && b.ms.size() > 1 &&
+                                (b.ms.size() * b.wpm > 4u || 4u * done.size() < ncu);
+            if (splits && (most == done.size() || b.ms.size() > done[most].second.ms.size())) most = i;
+        }
+        if (most == done.size()) break;
+        Bin &b = done[most].second, half{{}, b.wpm, b.tpl, b.pipe, b.share, b.hw};
+        half.ms.assign(b.ms.begin() + (ptrdiff_t)(b.ms.size() / 2), b.ms.end());
+        b.ms.resize(b.ms.size() / 2);
+        double c = 0;
+        for (uint32_t mm : half.ms) c = std::max(c, cost[mm]);
+        done.insert(done.begin() + (ptrdiff_t)most + 1, {c, half});  // (descriptor order, if it is kept)
+    }
     if (!keep)
         std::stable_sort(done.begin(), done.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
 
