@@ -2626,13 +2626,13 @@ struct AutoClass {
 //     waves 1.08, two 1.14, one 1.32; L = 64, A = 128, M = 960: two 0.83, one 0.96), and none for
 //     more than 8 below A = 2048 (L = 256, A = 1024, M = 256: 16 waves 1.09, 8 1.00); beyond
 //     M = 1575 the small ones keep one wave (L = 256, A = 128, M = 2048: two 1.43, one 1.23; L = 16,
-//     A = 256, M = 1600: two 1.57, one 1.22).  Not for mid-price markets of mostly NOISE agents with
+//     A = 256, M = 1600: two 1.57, one 1.31).  Not for mid-price markets of mostly NOISE agents with
 //     eight rows per wave: a row of marketable and other orders costs more in the bins than in the
-//     book (L = 64, A = 16384, M = 100: 7.1 with, 6.0 without).
+//     book (L = 16, A = 16384, M = 100: 7.2 with, 6.1 without).
 //     The clearing wave's share of the rows is what its clearing leaves of an even one.
 //   * In lock step three rows take four waves on a nearly empty chip (SplitMix64, L = 512, A = 192,
-//     M = 64: two 1.85, one 1.53, four 1.47), and many SplitMix64 markets one wave (L = 512, A = 512,
-//     M = 1600: two 2.74, one 2.43).
+//     M = 64: two 1.85, one 1.53, four 1.47), and many SplitMix64 markets one wave (L = 256, A = 512,
+//     M = 1600: two 2.74, one 2.49).
 //   * Large markets (32 rows or more) whose workgroups would leave the fullest CU with 15 % more than
 //     the mean take larger groups, of one market each.  L = 256, us per step for the share's power
 //     of two / this: A = 4096, M = 1200 7.7 / 6.2 (two waves, four), A = 16384, M = 600 14.5 / 13.1
@@ -2703,16 +2703,22 @@ AutoClass auto_class(uint32_t tpl, double A, double full, double noise, bool pla
 // share of the waves per market (twice when there are several markets per wave slot anyway).
 // Uneven ensembles (L 64..1024, A 64..16384), us per step of the rule above / this one: M = 256
 // 5.1 / 4.9, M = 1024 10.2 / 6.7, M = 4096 27 / 19; half A = 64, half A = 4096: M = 4096 17 / 12.
-AutoClass auto_class_mixed(double A, double full, double full_max, bool plain)
+// Mid-price markets of long books and wide offsets hold the chip in lock step, so on one that is not
+// nearly empty they get a wave per four rows (half A = 256, half L = 1024, A = 2048, M = 500: 4.3 for
+// two rows, 3.1).
+AutoClass auto_class_mixed(uint32_t tpl, double A, double full, double full_max, double noise, bool plain, bool mid)
 {
     const uint32_t rows = (uint32_t)std::ceil(A / 64.0);
     AutoClass c{1u, 0u};
     if (A <= 128.0) return c;
     uint32_t cap = 4u;
     while (cap < 16u && 2.0 * cap <= 1.1 * full_max) cap <<= 1;
-    const double w = std::min({(full_max < 2.5 ? 2.0 : 4.0) * full, (double)cap, plain ? rows / 2.0 : (double)rows});
+    const bool wide = plain && mid && tpl >= 16u && rows >= 16u && full_max <= 64.0;
+    const double lanes = wide ? rows / 4.0 : plain ? rows / 2.0 : rows;
+    const double w = std::min({(full_max < 2.5 ? 2.0 : 4.0) * full, (double)cap, lanes});
     while (2.0 * c.wpm <= w) c.wpm <<= 1;
-    if (c.wpm >= 2u && !plain) c.overlap = (uint32_t)std::max(1.0, 0.75 * A / 64.0 / c.wpm);
+    const bool slow_bins = mid && noise >= 0.75 && rows / c.wpm >= 8u;  // (see auto_class)
+    if (c.wpm >= 2u && !plain && !slow_bins) c.overlap = (uint32_t)std::max(1.0, 0.75 * A / 64.0 / c.wpm);
     return c;
 }
 
@@ -2819,7 +2825,7 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             const double full = 16.0 * ncu * (cost[c] / count[c]) / total;
             const double A = agents[c] / count[c];
             AutoClass a = dearest > 1.5 * total / M
-                              ? auto_class_mixed(A, full, 16.0 * ncu * dearest / total, plain[c])
+                              ? auto_class_mixed(1u << (c / 8u), A, full, 16.0 * ncu * dearest / total, noise[c] / agents[c], plain[c], mid[c])
                               : auto_class(1u << (c / 8u), A, full, noise[c] / agents[c], plain[c], mid[c]);
             // a caller's group size below what the class's markets need is refused further down
             if (t.waves_per_group && need[c] > t.waves_per_group) a.wpm = need[c];
