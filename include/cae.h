@@ -135,9 +135,10 @@ typedef struct cae_buffers {
 /* Schedule of the persistent launch.  Zero fields mean "choose automatically"; an
  * autotuner result can be passed back in.  A size class with waves_per_market, pipelined and pack
  * all 0 is left to the library, which then also chooses its overlap (unless given) and packing
- * (if every class is left to it); where waves_per_market is given, overlap and pack 0 mean off.  waves_per_market[c] applies to size class c
- * (class = index of the smallest of 64,128,256,512,1024 that is >= L, times 8, plus the
- * A bucket floor(log2(A)) clamped to 6..13 minus 6): 40 classes. */
+ * (if every class is left to it), both within max_lds_bytes; where waves_per_market is given,
+ * overlap and pack 0 mean off.  waves_per_market[c] applies to size class c (class = index of
+ * the smallest of 64,128,256,512,1024 that is >= L, times 8, plus the A bucket floor(log2(A))
+ * clamped to 6..13 minus 6): 40 classes. */
 #define CAE_NUM_CLASSES 40
 typedef struct cae_tuning {
     uint32_t waves_per_group;                   /* waves per workgroup (1..16)           */
@@ -324,9 +325,10 @@ int cae_mlp_refresh_weights(const cae_mlp *net, void *stream);
 int cae_mlp_forward(const cae_mlp *net, const float *x, float *y, uint32_t N, void *ws, void *stream);
 
 /* Inference only: y[N][d_out] = network(x[N][d_in]) in one fused launch (all three layers per
- * tile of 32 samples, activations kept on chip), with no workspace and no limit on N.  The
- * outputs are bit-identical to cae_mlp_forward's (same matrix-core tiles, summation order and
- * bfloat16 rounding points); nothing is kept for cae_mlp_backward.  Requires d_hidden <= 496.
+ * tile of 16 to 256 samples, activations kept on chip), with no workspace and no limit on N.  The
+ * outputs are bit-identical to cae_mlp_forward's: same bfloat16 rounding points, and the matrix
+ * instructions of the two (16x16x32 here, 16x16x32 or 32x32x16 there) add a sum's products in the
+ * same order.  Nothing is kept for cae_mlp_backward.  Requires d_hidden <= 496.
  * Asynchronous.  Errors: CAE_EINVAL (shape, NULL), CAE_EHIP. */
 int cae_mlp_predict(const cae_mlp *net, const float *x, float *y, uint32_t N, void *stream);
 
@@ -376,7 +378,8 @@ int cae_mlp_train_step_noalloc(const cae_mlp *net, const float *x, const float *
                                float eps, int loss_kind, float delta, float *loss, float *grads, void *stream);
 
 /* Mean loss over n values and its gradient with respect to y, r = y - target (device pointers;
- * one workgroup, fixed summation order).  Asynchronous.
+ * fixed summation order: one workgroup sums the loss, up to 512 others write a long gradient
+ * unless dy or loss lies inside another array).  Asynchronous.
  *   CAE_LOSS_MSE:   loss[0] = mean r^2, dy = 2 r / n
  *   CAE_LOSS_HUBER: loss[0] = mean of (r^2 / 2 if |r| <= delta else delta (|r| - delta / 2)),
  *                   dy = clamp(r, -delta, delta) / n   (delta > 0)

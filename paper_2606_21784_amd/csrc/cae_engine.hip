@@ -834,10 +834,12 @@ __device__ __forceinline__ void flush_any_lanes(const FlushLanesAny &a, int top,
 // (u = g + c, c) as pair 2u + c.  After the 2(2K+1) noise pairs: pair 0 marketable NOISE (buys
 // go to the top tick, sells to tick 0), pair 1 MOMENTUM by coin, pair 2 marketable MOMENTUM by
 // coin, pair 3 MAKER by side (section III-C's rules as in order_ctx).
-// PAIR generates two rows per pass, without branches: two independent generator chains for the
-// wave to issue from, where a row yields its four words together (Philox).  SplitMix64 mixes each
-// word by itself, so there the words a rule does not use are skipped by branching (four waves, L =
-// 256, A = 2000, M = 600, us per step: 5.2 in pairs, 4.7 so).
+// PAIR takes two rows per pass where a row yields its four words together (Philox); the compiler
+// still branches on the marketable orders between them.  With it and the one-pass flush callers'
+// overlapped schedules run 0.79 of the time of single rows and the general flush (K <= 13, 16
+// schedules of 64 to 1024 markets), 0.88 without that flush (K = 14 .. 120, 32 schedules, none
+// slower).  SplitMix64 mixes each word by itself, so there the words a rule does not use are skipped
+// by branching (four waves, L = 256, A = 2000, M = 600, us per step: 5.2 in pairs, 4.7 so).
 template <bool PAIR, typename Gen>
 __device__ __forceinline__ void gen_rel_mid(const DevMarket &d, uint32_t s, const Gen &gen, uint32_t b0,
                                             uint32_t stride, uint32_t end, uint32_t lane, uint32_t *H)
@@ -878,7 +880,6 @@ __device__ __forceinline__ void gen_rel_mid(const DevMarket &d, uint32_t s, cons
         const uint32_t word = a < d.n_noise ? noise : (a < mom_end ? mom : xb + 6u + ((a ^ s) & 1u));
         if (a < end) atomicAdd(&H[word], qty1(w2, d.Q));
     };
-    // (measured with the one-pass flush: see flush_lanes_any)
     for (uint32_t b = b0; b < end; b += 2u * stride) {
         uint32_t w0, w1, w2, w3, x0, x1, x2, x3;
         gen.words4_row(b, lane, w0, w1, w2, w3);
@@ -2025,18 +2026,21 @@ __device__ __forceinline__ void run_packed_seg(const EngineArgs &args, const Ite
                         gen.words4(a, w0, w1, w2, w3);
                         gen.words4(a2, v0, v1, v2, v3);
                         if (on) {
-                            const uint32_t w = a >= o.n_noise ? other_word<kLastOnly>(o, a, w0, w3) : noise_word(o, w0, w1);
+                            const uint32_t w = a >= o.n_noise ? other_word<kLastOnly>(o, a, w0, w3)
+                                                               : noise_word(o, w0, w1);
                             atomicAdd(&bk[pad_word(w)], order_qty(o, w2));
                         }
                         if (on2) {
-                            const uint32_t w = a2 >= o.n_noise ? other_word<kLastOnly>(o, a2, v0, v3) : noise_word(o, v0, v1);
+                            const uint32_t w = a2 >= o.n_noise ? other_word<kLastOnly>(o, a2, v0, v3)
+                                                               : noise_word(o, v0, v1);
                             atomicAdd(&bk[pad_word(w)], order_qty(o, v2));
                         }
                     } else {
                         if (on) {
                             uint32_t w0, w1, w2, w3 = 0;
                             gen.words4(a, w0, w1, w2, w3);
-                            const uint32_t w = a >= o.n_noise ? other_word<kLastOnly>(o, a, w0, w3) : noise_word(o, w0, w1);
+                            const uint32_t w = a >= o.n_noise ? other_word<kLastOnly>(o, a, w0, w3)
+                                                               : noise_word(o, w0, w1);
                             atomicAdd(&bk[pad_word(w)], order_qty(o, w2));
                         }
                         break;
@@ -2107,10 +2111,10 @@ __device__ __forceinline__ void run_packed(const EngineArgs &args, const Item &i
     else run_packed_seg<5, TRACE>(args, item, wave, lane, lds);
 }
 
-// FULL: the models and generators the markets may use (kLastOnly ..); TRACE: record the per-step series; PACK: some
-// items hold packed small markets (their per-lane generator and clearing need more vector
-// registers, so only ensembles that use them run this code).  Each instantiation carries only
-// the code it needs, which keeps registers for the step loop.
+// FULL: the models and generators the markets may use (kLastOnly ..); TRACE: record the per-step
+// series; PACK: some items hold packed small markets (their per-lane generator and clearing need
+// more vector registers, so only ensembles that use them run this code).  Each instantiation carries
+// only the code it needs, which keeps registers for the step loop.
 template <int TPL_MAX, int FULL, bool TRACE, bool PACK>
 __global__ void __launch_bounds__(1024) cae_engine_kernel(const EngineArgs args)
 {
@@ -2139,7 +2143,8 @@ __global__ void __launch_bounds__(1024) cae_engine_kernel(const EngineArgs args)
         } else if (item.wpm_log2 == 0) {
             if (active) run_market<TPL_MAX, false, FULL, TRACE>(args, item, sub, w_in, lane, true, lds);
         } else if (item.pipe == 2u) {
-            if constexpr (FULL != kLastOnly) run_market_ovl_any<TPL_MAX, FULL, TRACE>(args, item, sub, w_in, lane, active, lds);
+            if constexpr (FULL != kLastOnly)
+                run_market_ovl_any<TPL_MAX, FULL, TRACE>(args, item, sub, w_in, lane, active, lds);
             else run_market_ovl<TPL_MAX, TRACE>(args, item, sub, w_in, lane, active, lds);
         } else {
             run_market<TPL_MAX, true, FULL, TRACE>(args, item, sub, w_in, lane, active, lds);
@@ -2264,7 +2269,8 @@ __global__ void __launch_bounds__(64) cae_naive_kernel(const EngineArgs args, ui
     st.steps_done += args.S;
     args.state[m] = st;
     // the workgroup's end is its slowest market's
-    atomicMax(reinterpret_cast<unsigned long long *>(args.clk) + 2u * blockIdx.x + 1u, (unsigned long long)wall_clock64());
+    atomicMax(reinterpret_cast<unsigned long long *>(args.clk) + 2u * blockIdx.x + 1u,
+              (unsigned long long)wall_clock64());
 }
 
 // One clearing pass over n books of L ticks, the books in registers from memory to memory.  Books
@@ -2583,10 +2589,12 @@ EngineFn engine_fn_t(uint32_t tpl_max, bool pack)
 }
 
 // The instantiation for the largest book, with mid-price or SplitMix64 code only when some market
-// uses that model or generator, trace stores only for cae_step_traced and the packed path only when items use it.
+// uses that model or generator, trace stores only for cae_step_traced and the packed path only when
+// items use it.
 EngineFn engine_fn(uint32_t tpl_max, int full, bool trace, bool pack)
 {
-    if (full == kAnyGen) return trace ? engine_fn_t<kAnyGen, true>(tpl_max, pack) : engine_fn_t<kAnyGen, false>(tpl_max, pack);
+    if (full == kAnyGen)
+        return trace ? engine_fn_t<kAnyGen, true>(tpl_max, pack) : engine_fn_t<kAnyGen, false>(tpl_max, pack);
     if (full == kAnyModel)
         return trace ? engine_fn_t<kAnyModel, true>(tpl_max, pack) : engine_fn_t<kAnyModel, false>(tpl_max, pack);
     return trace ? engine_fn_t<kLastOnly, true>(tpl_max, pack) : engine_fn_t<kLastOnly, false>(tpl_max, pack);
@@ -2786,7 +2794,8 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     // from its share of the ensemble's cost
     bool auto_c[CAE_NUM_CLASSES] = {};
     {
-        double cost[CAE_NUM_CLASSES] = {}, agents[CAE_NUM_CLASSES] = {}, noise[CAE_NUM_CLASSES] = {}, total = 0.0, dearest = 0.0;
+        double cost[CAE_NUM_CLASSES] = {}, agents[CAE_NUM_CLASSES] = {}, noise[CAE_NUM_CLASSES] = {};
+        double total = 0.0, dearest = 0.0;
         uint32_t count[CAE_NUM_CLASSES] = {}, need[CAE_NUM_CLASSES] = {}, bins[CAE_NUM_CLASSES] = {}, A_max = 0;
         bool plain[CAE_NUM_CLASSES] = {}, mid[CAE_NUM_CLASSES] = {}, all_auto = true, small_last = maxL <= kPackMaxL;
         for (uint32_t m = 0; m < M; ++m) {
@@ -2824,9 +2833,11 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             }
             const double full = 16.0 * ncu * (cost[c] / count[c]) / total;
             const double A = agents[c] / count[c];
+            const uint32_t tpl = 1u << (c / 8u);
+            const double pn = noise[c] / agents[c];
             AutoClass a = dearest > 1.5 * total / M
-                              ? auto_class_mixed(1u << (c / 8u), A, full, 16.0 * ncu * dearest / total, noise[c] / agents[c], plain[c], mid[c])
-                              : auto_class(1u << (c / 8u), A, full, noise[c] / agents[c], plain[c], mid[c]);
+                              ? auto_class_mixed(tpl, A, full, 16.0 * ncu * dearest / total, pn, plain[c], mid[c])
+                              : auto_class(tpl, A, full, pn, plain[c], mid[c]);
             // a caller's group size below what the class's markets need is refused further down
             if (t.waves_per_group && need[c] > t.waves_per_group) a.wpm = need[c];
             while (t.waves_per_group && need[c] <= t.waves_per_group && a.wpm > t.waves_per_group) a.wpm >>= 1;
@@ -2869,7 +2880,8 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     }
     uint32_t G = t.waves_per_group;
     if (G == 0) G = std::max(wpm_max, 4u);
-    if (G > 16 || G < wpm_max) return fail(CAE_EINVAL, "waves_per_group=%u must be in [max waves_per_market=%u, 16]", G, wpm_max);
+    if (G > 16 || G < wpm_max)
+        return fail(CAE_EINVAL, "waves_per_group=%u must be in [max waves_per_market=%u, 16]", G, wpm_max);
     bool any_pipe = false;
     for (uint32_t c = 0; c < CAE_NUM_CLASSES; ++c) any_pipe |= t.pipelined[c] != 0;
     if (any_pipe && G < 2) return fail(CAE_EINVAL, "pipelined classes need waves_per_group >= 2");
@@ -3026,7 +3038,8 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
     e->lds_bytes = lds_max;
 
     int per_cu = 0;
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(engine_fn(tpl_max, e->full, false, e->any_pack)),
+    const EngineFn fn = engine_fn(tpl_max, e->full, false, e->any_pack);
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(fn),
                                                          (int)(G * 64u), (size_t)lds_max));
     if (per_cu < 1) return fail(CAE_EINVAL, "schedule does not fit on a CU (lds %u B, %u waves)", lds_max, G);
     if (t.groups_per_cu) per_cu = std::min<int>(per_cu, (int)t.groups_per_cu);

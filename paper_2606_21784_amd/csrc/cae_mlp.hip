@@ -424,7 +424,8 @@ __global__ void __launch_bounds__(256) mlp_out(const uint16_t *h, const uint16_t
 #pragma unroll
         for (uint32_t c = 0; c < 8u; ++c) {
             const uint32_t e = e0 + 256u * c;
-            if (e < 16u * NB * hc) *reinterpret_cast<uint4 *>(hs + e / hc * ldh + 8u * (e % hc)) = keep(8u * (e % hc) < H, v[c]);
+            if (e >= 16u * NB * hc) continue;
+            *reinterpret_cast<uint4 *>(hs + e / hc * ldh + 8u * (e % hc)) = keep(8u * (e % hc) < H, v[c]);
         }
     }
     if (dout == 16u) {
