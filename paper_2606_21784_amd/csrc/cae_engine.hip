@@ -2950,27 +2950,57 @@ int build_schedule(cae_ensemble *e, const cae_tuning *tn, const uint32_t *ids,
             for (uint32_t mm : b.ms) c = std::max(c, cost[mm]);
             done.push_back({c, b});
         }
-    // Fewer items than CUs: the fullest ones are halved, those of more than four waves until every CU
-    // has an item, the others (a wave or less per SIMD) until every fourth one has.  The group size
-    // follows the largest markets, so the small ones of a mixture would share a few CUs at 16 waves
-    // each (a tenth A = 4096, the rest A = 256, L = 1024, M = 256, us per step: 5.6, spread out 3.6);
-    // L = 256, A = 300, M = 32 SplitMix64 ones of one wave: 1.68 in fours, 1.58 alone.  Beyond 64 items the
-    // markets of one CU do not hold each other up (M = 256 on one wave: 1 to 3 % slower alone).
-    while (done.size() < ncu) {
-        size_t most = done.size();
-        for (size_t i = 0; i < done.size(); ++i) {
-            const Bin &b = done[i].second;
-            const bool splits = (b.pipe == 0u || b.pipe == 2u) && b.ms.size() > 1 &&
-                                (b.ms.size() * b.wpm > 4u || 4u * done.size() < ncu);
-            if (splits && (most == done.size() || b.ms.size() > done[most].second.ms.size())) most = i;
+    // Fewer items than CUs: the costliest ones are halved, those of more than four waves until every CU
+    // has an item, smaller ones of several waves per market until every fourth one has.  The group
+    // size follows the largest markets, so the small ones of a mixture would share a few CUs at 16
+    // waves each (a tenth A = 4096, the rest A = 256, L = 1024, M = 256, us per step: 5.6, spread out
+    // 3.6); two SplitMix64 markets of L = 512, A = 4096 on two waves each: 9.2 in one workgroup, 8.4
+    // in two.  Items of up to four single waves stay together: apart they are 6 % faster in long
+    // launches (A = 300, M = 32) and 5 % slower in launches of one step (A = 100: 5.1, 5.3).  Halving
+    // the items of most markets instead is never faster and up to 1.4 times slower (L 16..512, A 64..
+    // 4096, M = 500, mid-price: 4.0, 2.9).
+    if (done.size() < ncu) {
+        struct Part { size_t bin, at, n; };  // markets [at, at + n) of a bin
+        const auto later = [](const Part &x, const Part &y) { return x.bin != y.bin ? x.bin > y.bin : x.at > y.at; };
+        const auto load = [&](const Part &x) { return x.n < 2u ? 0.0 : (double)x.n * cost[done[x.bin].second.ms[x.at]]; };
+        const auto smaller = [&](const Part &x, const Part &y) {
+            const double lx = load(x), ly = load(y);
+            return lx != ly ? lx < ly : later(x, y);
+        };
+        std::vector<Part> parts, kept;
+        for (size_t i = 0; i < done.size(); ++i) parts.push_back({i, 0, done[i].second.ms.size()});
+        std::make_heap(parts.begin(), parts.end(), smaller);
+        while (!parts.empty()) {
+            std::pop_heap(parts.begin(), parts.end(), smaller);
+            const Part p = parts.back();
+            parts.pop_back();
+            const Bin &b = done[p.bin].second;
+            const size_t items_now = parts.size() + kept.size() + 1u;
+            const bool halves = p.n > 1u && items_now < ncu && (b.pipe == 0u || b.pipe == 2u) &&
+                                (p.n * b.wpm > 4u || (b.wpm > 1u && 4u * items_now < ncu));
+            if (!halves) {
+                kept.push_back(p);
+                continue;
+            }
+            for (const Part &q : {Part{p.bin, p.at, p.n / 2u}, Part{p.bin, p.at + p.n / 2u, p.n - p.n / 2u}}) {
+                parts.push_back(q);
+                std::push_heap(parts.begin(), parts.end(), smaller);
+            }
         }
-        if (most == done.size()) break;
-        Bin &b = done[most].second, half{{}, b.wpm, b.tpl, b.pipe, b.share, b.hw};
-        half.ms.assign(b.ms.begin() + (ptrdiff_t)(b.ms.size() / 2), b.ms.end());
-        b.ms.resize(b.ms.size() / 2);
-        double c = 0;
-        for (uint32_t mm : half.ms) c = std::max(c, cost[mm]);
-        done.insert(done.begin() + (ptrdiff_t)most + 1, {c, half});  // (descriptor order, if it is kept)
+        if (kept.size() > done.size()) {
+            std::sort(kept.begin(), kept.end(), [&](const Part &x, const Part &y) { return later(y, x); });
+            std::vector<std::pair<double, Bin>> spread;
+            spread.reserve(kept.size());
+            for (const Part &q : kept) {
+                const Bin &b = done[q.bin].second;
+                Bin x{{}, b.wpm, b.tpl, b.pipe, b.share, b.hw};
+                x.ms.assign(b.ms.begin() + (ptrdiff_t)q.at, b.ms.begin() + (ptrdiff_t)(q.at + q.n));
+                double c = 0;
+                for (uint32_t mm : x.ms) c = std::max(c, cost[mm]);
+                spread.push_back({c, std::move(x)});
+            }
+            done.swap(spread);
+        }
     }
     if (!keep)
         std::stable_sort(done.begin(), done.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
