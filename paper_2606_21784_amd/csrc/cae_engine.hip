@@ -2711,9 +2711,11 @@ AutoClass auto_class(uint32_t tpl, double A, double full, double noise, bool pla
 // share of the waves per market (twice when there are several markets per wave slot anyway).
 // Uneven ensembles (L 64..1024, A 64..16384), us per step of the rule above / this one: M = 256
 // 5.1 / 4.9, M = 1024 10.2 / 6.7, M = 4096 27 / 19; half A = 64, half A = 4096: M = 4096 17 / 12.
-// Mid-price markets of long books and wide offsets hold the chip in lock step, so on one that is not
-// nearly empty they get a wave per four rows (half A = 256, half L = 1024, A = 2048, M = 500: 4.3 for
-// two rows, 3.1).
+// Mid-price markets of long books and wide offsets hold the chip in lock step, so on one that is
+// neither nearly empty nor full they get a wave per four rows (half A = 256, half L = 1024, A = 2048,
+// M = 500: 4.3 for two rows, 3.1; L 16..1024, A 64..2048, M = 1000: 4.0, 4.5).  Markets of four rows whose share is less than four waves take two (L = 64, a tenth
+// A = 4096, the rest A = 256, M = 1000: 2.6 with four, 2.2; 19 in 20 A = 256, the rest 2048, L = 256,
+// M = 2000: 2.4, 1.8).
 AutoClass auto_class_mixed(uint32_t tpl, double A, double full, double full_max, double noise, bool plain, bool mid)
 {
     const uint32_t rows = (uint32_t)std::ceil(A / 64.0);
@@ -2721,8 +2723,9 @@ AutoClass auto_class_mixed(uint32_t tpl, double A, double full, double full_max,
     if (A <= 128.0) return c;
     uint32_t cap = 4u;
     while (cap < 16u && 2.0 * cap <= 1.1 * full_max) cap <<= 1;
-    const bool wide = plain && mid && tpl >= 16u && rows >= 16u && full_max <= 64.0;
-    const double lanes = wide ? rows / 4.0 : plain ? rows / 2.0 : rows;
+    const bool wide = plain && mid && tpl >= 16u && rows >= 16u && full_max >= 12.0 && full_max <= 64.0;
+    double lanes = wide ? rows / 4.0 : plain ? rows / 2.0 : rows;
+    if (!plain && rows == 4u && full < 4.0) lanes = 2.0;
     const double w = std::min({(full_max < 2.5 ? 2.0 : 4.0) * full, (double)cap, lanes});
     while (2.0 * c.wpm <= w) c.wpm <<= 1;
     const bool slow_bins = mid && noise >= 0.75 && rows / c.wpm >= 8u;  // (see auto_class)

@@ -46,3 +46,15 @@ def test_mixed_mid_price(big, small, n_big, n_small, w, overlapped):
     t = _check(E, d, None, S=3)
     c = E.size_class(*big[:2])
     assert t["waves_per_market"][c] == w and (t["overlap"].get(c, 0) > 0) == overlapped
+
+
+@pytest.mark.parametrize("n_big,n_small,w", [(0.4, 3.5, 2), (0.1, 0.5, 4)])
+def test_mixed_four_rows(n_big, n_small, w):
+    """Last-tick markets of four rows of agents beside large ones: two waves where a share of the
+    chip's waves in proportion to cost would be less than four (2.0; 10.2 in the second ensemble)."""
+    import torch
+    E = _engine()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    d = np.concatenate([E.markets(64, 4096, 4, 7, M=int(n_big * cus)), E.markets(64, 256, 4, 7, n_noise=200, n_mom=30, M=int(n_small * cus))])
+    t = _check(E, d, None, S=3)
+    assert t["waves_per_market"][E.size_class(64, 256)] == w
