@@ -2713,9 +2713,9 @@ AutoClass auto_class(uint32_t tpl, double A, double full, double noise, bool pla
 // 5.1 / 4.9, M = 1024 10.2 / 6.7, M = 4096 27 / 19; half A = 64, half A = 4096: M = 4096 17 / 12.
 // Mid-price markets of long books and wide offsets hold the chip in lock step, so on one that is
 // neither nearly empty nor full they get a wave per four rows (half A = 256, half L = 1024, A = 2048,
-// M = 500: 4.3 for two rows, 3.1; L 16..1024, A 64..2048, M = 1000: 4.0, 4.5).  Markets of four rows whose share is less than four waves take two (L = 64, a tenth
-// A = 4096, the rest A = 256, M = 1000: 2.6 with four, 2.2; 19 in 20 A = 256, the rest 2048, L = 256,
-// M = 2000: 2.4, 1.8).
+// M = 500: 4.3 for two rows, 3.1; L 16..1024, A 64..2048, M = 1000: 4.0, 4.5).  Markets of four rows
+// whose share is less than four waves take two (L = 64, a tenth A = 4096, the rest A = 256, M = 1000:
+// 2.6 with four, 2.2; 19 in 20 A = 256, the rest 2048, L = 256, M = 2000: 2.4, 1.8).
 AutoClass auto_class_mixed(uint32_t tpl, double A, double full, double full_max, double noise, bool plain, bool mid)
 {
     const uint32_t rows = (uint32_t)std::ceil(A / 64.0);
